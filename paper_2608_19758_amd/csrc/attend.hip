@@ -21,7 +21,8 @@
 // with one workgroup barrier per step. The copy addresses come from small LDS
 // tables filled once per chunk of steps (kept block index and its page-table
 // entries, or the compacted list of pruned blocks), read one step ahead, so
-// nothing in the loop waits on a global load.
+// nothing in the loop waits on a global load. Where the 64 rows of a step are
+// one run of the pool the step's base address is scalar (KeptCopier).
 //
 // Per step:
 //  - S^T = K Q^T on the matrix cores (A = key rows from LDS, B = the wave's
@@ -87,7 +88,12 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 __device__ __forceinline__ int kslot16(int r, int c) { return r * 16 + (c ^ (r & 15)); }
 __device__ __forceinline__ int vslot16(int r, int c) { return r * 16 + (c ^ (4 * (r & 3))); }
 __device__ __forceinline__ int kslot8(int r, int c) { return r * 8 + (c ^ ((r >> 1) & 7)); }
-__device__ __forceinline__ int vslot8(int r, int c) { return r * 8 + (c ^ (2 * ((r >> 1) & 3))); }
+// (V fp8: a transposing read of 32 lanes takes 32 bytes of rows {0-3, 8-11} or
+// {4-7, 12-15} of a 16-row group; with row bits 1 and 3 in the swizzle those
+// eight rows lie on disjoint banks: 246 B/clk/CU, against 127 with row bits 1
+// and 2, which put rows 8 apart on the same banks)
+__device__ __forceinline__ int vswz8(int r) { return 2 * (((r >> 1) & 1) | ((r >> 2) & 2)); }
+__device__ __forceinline__ int vslot8(int r, int c) { return r * 8 + (c ^ vswz8(r)); }
 
 // Wait until at most N vector-memory operations of this wave are in flight.
 template <int N>
@@ -121,6 +127,12 @@ __device__ __forceinline__ void dma16(const void* g, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds)
                : "memory", "m0");
 }
+
+// The same with a uniform base address and a 32-bit byte offset per lane.
+__device__ __forceinline__ void dma16s(const uint8_t* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds)
+               : "memory", "m0");
+}
 #pragma clang diagnostic pop
 
 // Copy plan of one 64-row step (K and V): copy instruction j of wave w moves
@@ -137,48 +149,113 @@ struct CopyPlan {
   __device__ static int row(int j, int tid) { return RPG * ((tid >> 6) + W * j) + (tid & 63) / CPR; }
 };
 
-// Start the copies of one step: row row(j) of K / V lies at byte offset
-// off[j] from Kb / Vb.
-template <int W, int FP8, int RING>
-__device__ __forceinline__ void issue_copies(uint32_t st, const uint8_t* Kb, const uint8_t* Vb,
-                                             const int64_t (&off)[CopyPlan<W, FP8, RING>::PER], int tid) {
-  using P = CopyPlan<W, FP8, RING>;
-  const int w = tid >> 6, lane = tid & 63;
-  const uint32_t wu = __builtin_amdgcn_readfirstlane(w);   // wave index, uniform
-  const int pc = lane % P::CPR;
-#pragma unroll
-  for (int j = 0; j < P::PER; ++j) {
-    const int g = w + W * j;
-    const int r = P::RPG * g + lane / P::CPR;
-    const int kc = FP8 ? (pc ^ ((r >> 1) & 7)) : (pc ^ (r & 15));
-    const int vc = FP8 ? (pc ^ (2 * ((r >> 1) & 3))) : (pc ^ (4 * (r & 3)));
-    const uint32_t gl = st + (wu + W * j) * 64 * 16;
-    dma16(Kb + off[j] + 16 * kc, gl);
-    dma16(Vb + off[j] + 16 * vc, gl + 64 * P::CPR * 16);
-  }
-}
+// 16-byte chunk of a row that lane slot pc of the row's K / V copy fetches
+// (the swizzles above).
+template <int FP8>
+__device__ __forceinline__ int kchunk(int r, int pc) { return FP8 ? (pc ^ ((r >> 1) & 7)) : (pc ^ (r & 15)); }
+template <int FP8>
+__device__ __forceinline__ int vchunk(int r, int pc) { return FP8 ? (pc ^ vswz8(r)) : (pc ^ (4 * (r & 3))); }
 
-// Copy addresses of a step come in two parts: fetch(s, r) reads the table
-// entry of row r of step s from LDS, addr(entry, s, r) turns it into the byte
-// offset. The entries of the next step are fetched before a step is computed
-// and converted after the next barrier, so their LDS latency is never waited
-// on.
-template <int W, int FP8, int RING, class Fetch, class Addr>
-struct Addresser {
+// The copies of a step come in two parts: get(s) reads the step's address
+// record from LDS, issue(stage) turns it into addresses and starts the
+// copies into the stage at LDS byte address `stage`. The record of the next
+// step is read before a step is computed and used after the next barrier, so
+// its LDS latency is never waited on.
+//
+// KeptCopier: the 64 rows of half of a kept block. Where they lie one after
+// the other in the pool (rph == 1: contiguous K/V, or pages of a power of two
+// >= 64 tokens) the step's base is uniform: it goes into scalar registers,
+// the per-lane part is a constant, and a copy costs no vector instruction
+// (128K fp8 prefill at 4% kept 5.20 -> 5.07 ms against 64-bit per-lane
+// addresses; a 4096-step run of the fp8 loop 2620 -> 2350 clocks a step,
+// without any copies 2190).
+// Otherwise every row group has a record of its own and every lane its
+// 64-bit address.
+template <int W, int FP8, int RING>
+struct KeptCopier {
   using P = CopyPlan<W, FP8, RING>;
-  using Raw = decltype(std::declval<Fetch>()(0, 0));
-  Fetch fetch;
-  Addr addr;
+  const uint4* rec;           // records of the chunk of kept blocks
+  const uint8_t *K, *V;
+  int rph, gshift, rowb;      // records per half, log2 rows per record, bytes per token slot
   int tid;
-  Raw raw[P::PER];
-  int64_t off[P::PER];
+  uint32_t wu;                // wave index, uniform
+  int r0b, k16, v16;          // this lane's first row and its K / V chunk, in bytes
+  uint4 raw[P::PER];
+  __device__ __forceinline__ KeptCopier(const uint4* rec_, const uint8_t* K_, const uint8_t* V_, int rph_,
+                                        int gshift_, int rowb_, int tid_)
+      : rec(rec_), K(K_), V(V_), rph(rph_), gshift(gshift_), rowb(rowb_), tid(tid_),
+        wu(__builtin_amdgcn_readfirstlane(tid_ >> 6)) {
+    // the rows of copy j lie W * RPG * j further, a multiple of 16: same swizzle
+    static_assert(P::PER == 1 || W * P::RPG % 16 == 0, "swizzle period");
+    const int r = P::row(0, tid), pc = (tid & 63) % P::CPR;
+    r0b = r * rowb;
+    k16 = 16 * kchunk<FP8>(r, pc);
+    v16 = 16 * vchunk<FP8>(r, pc);
+  }
   __device__ __forceinline__ void get(int s) {
 #pragma unroll
-    for (int j = 0; j < P::PER; ++j) raw[j] = fetch(s, P::row(j, tid));
+    for (int j = 0; j < P::PER; ++j) raw[j] = rec[s * rph + (P::row(j, tid) >> gshift)];
   }
-  __device__ __forceinline__ void convert(int s) {
+  __device__ __forceinline__ void issue(uint32_t st) const {
+    const uint32_t gl = st + wu * 64 * 16;
+    if (rph == 1) {
+      const uint32_t lo = __builtin_amdgcn_readfirstlane(raw[0].x);
+      const uint32_t hi = __builtin_amdgcn_readfirstlane(raw[0].y);
+      const int lim = __builtin_amdgcn_readfirstlane(raw[0].z);
+      const int64_t base = (int64_t)(((uint64_t)hi << 32) | lo);
+      if (lim >= (kStep - 1) * rowb) {
 #pragma unroll
-    for (int j = 0; j < P::PER; ++j) off[j] = addr(raw[j], s, P::row(j, tid));
+        for (int j = 0; j < P::PER; ++j) {
+          const int64_t bj = base + j * W * P::RPG * rowb;
+          dma16s(K + bj, r0b + k16, gl + W * j * 64 * 16);
+          dma16s(V + bj, r0b + v16, gl + (W * j + P::CPR) * 64 * 16);
+        }
+      } else {                // the sequence ends inside the half: repeat its last row
+#pragma unroll
+        for (int j = 0; j < P::PER; ++j) {
+          const int o = min(r0b + j * W * P::RPG * rowb, lim);
+          dma16s(K + base, o + k16, gl + W * j * 64 * 16);
+          dma16s(V + base, o + v16, gl + (W * j + P::CPR) * 64 * 16);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < P::PER; ++j) {
+        // both operands of min are >= 0
+        const int64_t off = (int64_t)(((uint64_t)raw[j].y << 32) | raw[j].x) +
+                            (uint32_t)min(r0b + j * W * P::RPG * rowb, (int)raw[j].z);
+        dma16(K + off + k16, gl + W * j * 64 * 16);
+        dma16(V + off + v16, gl + (W * j + P::CPR) * 64 * 16);
+      }
+    }
+  }
+};
+
+// MeanCopier: 64 block means per step, gathered through the list of pruned
+// blocks (32-bit offsets from the unit's first mean).
+template <int W, int FP8, int RING>
+struct MeanCopier {
+  using P = CopyPlan<W, FP8, RING>;
+  const uint16_t* list;
+  const uint8_t *K, *V;
+  int np;                     // blocks in the list
+  int tid;
+  int raw[P::PER];
+  __device__ __forceinline__ void get(int s) {
+#pragma unroll   // past the list: repeat a valid entry
+    for (int j = 0; j < P::PER; ++j) raw[j] = list[min(kStep * s + P::row(j, tid), np - 1)];
+  }
+  __device__ __forceinline__ void issue(uint32_t st) const {
+    const int pc = (tid & 63) % P::CPR;
+    const uint32_t wu = __builtin_amdgcn_readfirstlane(tid >> 6);
+#pragma unroll
+    for (int j = 0; j < P::PER; ++j) {
+      const int r = P::row(j, tid);
+      const int off = raw[j] * (kHeadDim * (FP8 ? 1 : 2));
+      const uint32_t gl = st + (wu + W * j) * 64 * 16;
+      dma16s(K, off + 16 * kchunk<FP8>(r, pc), gl);
+      dma16s(V, off + 16 * vchunk<FP8>(r, pc), gl + 64 * P::CPR * 16);
+    }
   }
 };
 
@@ -195,30 +272,28 @@ constexpr int copy_lead(int W, int FP8, int nst) {
 // Ring over steps 0 .. n-1 without cross-step overlap of the compute;
 // body(stage, s) consumes step s. Ends with a barrier (the ring may be
 // refilled).
-template <int W, int FP8, int RING, int LEAD_SET = 0, class Fetch, class Addr, class Body>
-__device__ __forceinline__ void ring_loop(uint4* ring, int n, const uint8_t* Kb, const uint8_t* Vb,
-                                          Fetch fetch, Addr addr, Body body, int tid) {
+template <int W, int FP8, int RING, int LEAD_SET = 0, class Copier, class Body>
+__device__ __forceinline__ void ring_loop(uint4* ring, int n, Copier cp, Body body) {
   using P = CopyPlan<W, FP8, RING>;
   constexpr int LEAD = LEAD_SET > 0 ? LEAD_SET : copy_lead(W, FP8, P::NST);
   static_assert(LEAD >= 1 && LEAD <= P::NST - 1 && LEAD <= 6, "copy lead");
-  Addresser<W, FP8, RING, Fetch, Addr> ad{fetch, addr, tid};
   const uint32_t ring_lds = (uint32_t)(uintptr_t)(lds_void_t*)ring;   // LDS byte address
   int ni = 0;
 #pragma unroll 1
   for (; ni < LEAD && ni < n; ++ni) {
-    ad.get(ni);
-    ad.convert(ni);
-    issue_copies<W, FP8, RING>(ring_lds + ni * P::STAGE * 16, Kb, Vb, ad.off, tid);
+    cp.get(ni);
+    cp.issue(ring_lds + ni * P::STAGE * 16);
   }
-  if (ni < n) ad.get(ni);
+  if (ni < n) cp.get(ni);
 #pragma unroll 1
   for (int s = 0; s < n; ++s) {
-    wait_ahead<P::D>(ni - 1 - s);
+    // LEAD - 1 later steps are in flight except at the end of the list
+    if (ni - 1 - s == LEAD - 1) wait_vmcnt<(LEAD - 1) * P::D>();
+    else wait_ahead<P::D>(ni - 1 - s);
     lds_barrier();   // step s visible to all; every wave is done with step s-1
     if (ni < n) {
-      ad.convert(ni);
-      issue_copies<W, FP8, RING>(ring_lds + (ni++ % P::NST) * P::STAGE * 16, Kb, Vb, ad.off, tid);
-      if (ni < n) ad.get(ni);   // lands while the step is computed
+      cp.issue(ring_lds + (ni++ % P::NST) * P::STAGE * 16);
+      if (ni < n) cp.get(ni);   // lands while the step is computed
     }
     body(ring + (s % P::NST) * P::STAGE, s);
   }
@@ -616,15 +691,13 @@ __device__ __forceinline__ void fin_fp8(const uint4* st, Scores<RT>& S, RowState
 
 // Steps 0 .. n-1 of a ring: the scores of a step (qk) then the rest of it
 // (fin). The two waves of a SIMD overlap each other's matrix and vector work.
-template <int W, int FP8, int RT, int RING, int LEAD_SET = 0, class Fetch, class Addr, class QK,
-          class Fin>
-__device__ __forceinline__ void run_steps(uint4* ring, int n, const uint8_t* Kb, const uint8_t* Vb,
-                                          Fetch fetch, Addr addr, QK qk, Fin fin, int tid) {
-  ring_loop<W, FP8, RING, LEAD_SET>(ring, n, Kb, Vb, fetch, addr, [&](const uint4* st, int s) {
+template <int W, int FP8, int RT, int RING, int LEAD_SET = 0, class Copier, class QK, class Fin>
+__device__ __forceinline__ void run_steps(uint4* ring, int n, const Copier& cp, QK qk, Fin fin) {
+  ring_loop<W, FP8, RING, LEAD_SET>(ring, n, cp, [&](const uint4* st, int s) {
     Scores<RT> S;
     qk(st, S);
     fin(st, S, s);
-  }, tid);
+  });
 }
 
 template <int FP8, int W, int RT>
@@ -832,36 +905,28 @@ __global__ __launch_bounds__(64 * W, wgs_per_cu(W, FP8)) void attend_kernel(Prob
           aux[k] = make_uint4((uint32_t)base, (uint32_t)((uint64_t)base >> 32), lim, 0u);
         }
         __syncthreads();
-        auto fetch = [&](int s, int r) -> uint4 { return aux[(s * rph) + (r >> gshift)]; };
         const int rowb = (int)rowbytes;   // <= 2^18 (Hkv <= 1024), so 63 * rowb fits int32
-        auto addr = [&](uint4 rec, int s, int r) -> int64_t {
-          (void)s;
-          const int64_t base = (int64_t)(((uint64_t)rec.y << 32) | rec.x);
-          // r * rowb is fixed per lane; both operands of min are >= 0
-          return base + (uint32_t)min(r * rowb, (int)rec.z);
-        };
         const int nst = 2 * nbc;
+        const KeptCopier<W, FP8, RING> cp(aux, K, V, rph, gshift, rowb, tid);
         if constexpr (FP8) {
           run_steps<W, 1, RT, RING>(
-              ring, nst, K, V, fetch, addr,
+              ring, nst, cp,
               [&](const uint4* st, Scores<RT>& S) { qk_fp8<RT>(st, qf, S, ol); },
               [&](const uint4* st, Scores<RT>& S, int s) {
                 const int wp = c0 + (s >> 1);   // walk position of the step's block
                 fin_fp8<0, RT>(st, S, rs, cs, (wp == 0 ? e0 : e1) * kBlock + kStep * (s & 1), pos,
                                wp < nmask, lane, sel, ol);
-              },
-              tid);
+              });
         } else {
           run_steps<W, 0, RT, RING, W == 8 ? 1 : 0>(   // bf16 kept steps: one step ahead
-              ring, nst, K, V, fetch, addr,
+              ring, nst, cp,
               [&](const uint4* st, Scores<RT>& S) { qk_bf16<RT>(st, qb, S, lane); },
               [&](const uint4* st, Scores<RT>& S, int s) {
                 const int wp = c0 + (s >> 1);   // walk position of the step's block
                 fin_bf16<0, RT, NPRE>(st, S, rs, cs, off, 1.f,
                                       (wp == 0 ? e0 : e1) * kBlock + kStep * (s & 1), pos,
                                       wp < nmask, 0, lane);
-              },
-              tid);
+              });
         }
       }
     }
@@ -920,31 +985,24 @@ __global__ __launch_bounds__(64 * W, wgs_per_cu(W, FP8)) void attend_kernel(Prob
           __syncthreads();
         }
         if (np == 0) continue;
-        // past the list: repeat a valid entry
-        auto fetch = [&](int s, int r) -> int { return plist[min(kStep * s + r, np - 1)]; };
-        auto addr = [&](int J, int s, int r) -> int64_t {
-          (void)s;
-          (void)r;
-          return (int64_t)J * kHeadDim * (FP8 ? 1 : 2);
-        };
+        const MeanCopier<W, FP8, RING> cp{plist, Kh, Vh, np, tid, {}};
+        const int nst = (np + kStep - 1) / kStep;
         if constexpr (FP8) {
           run_steps<W, 1, RT, RING>(
-              ring, (np + kStep - 1) / kStep, Kh, Vh, fetch, addr,
+              ring, nst, cp,
               [&](const uint4* st, Scores<RT>& S) { qk_fp8<RT>(st, qf, S, ol); },
               [&](const uint4* st, Scores<RT>& S, int s) {
                 const int nv = np - kStep * s;
                 fin_fp8<1, RT>(st, S, rs, cs, 0, pos, nv < kStep, lane, sel, ol, nv);
-              },
-              tid);
+              });
         } else {
           run_steps<W, 0, RT, RING>(
-              ring, (np + kStep - 1) / kStep, Kh, Vh, fetch, addr,
+              ring, nst, cp,
               [&](const uint4* st, Scores<RT>& S) { qk_bf16<RT>(st, qb, S, lane); },
               [&](const uint4* st, Scores<RT>& S, int s) {
                 fin_bf16<1, RT, NPRE>(st, S, rs, cs, off, 1.f, 0, pos, false, np - kStep * s,
                                       lane);
-              },
-              tid);
+              });
         }
       }
     }
