@@ -72,10 +72,10 @@
  * usual log-sum-exp weights. The result equals the unsplit one up to
  * rounding (fp8: P~ is rounded against each part's own maximum).
  * kv_splits == 0 (the default) plans on the device after the selection:
- * only units costlier than a step budget are split, the budget being set by
- * the call's total cost over about four items per compute unit (so a short
- * chunk after a long prefix, or a few dense heads, no longer bound the run
- * time). kv_splits == n >= 1 cuts every unit into n parts (1 = no splits).
+ * only units costlier than a step budget are split, the budget being one
+ * resident workgroup's share of the call's total cost (so a short chunk after
+ * a long prefix, or a few dense heads, do not bound the run time), into at most
+ * 64 parts. kv_splits == n >= 1 cuts every unit into n parts (1 = no splits).
  *
  * Query tiles (Sec. 3.3 PackGQA and the per-tile index of Eq. csr)
  * --------------------------------------------------------------

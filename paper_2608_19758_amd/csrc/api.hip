@@ -53,7 +53,7 @@ int nbk_of(const fp2_params_t* p) { return (max_kv_of(p) + fp2::kBlock - 1) / fp
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-constexpr int kMaxSplits = 32;            // parts per unit (one per lane of the combine)
+constexpr int kMaxSplits = 32;            // largest kv_splits
 constexpr size_t kPartialRows = 65536;    // packed rows of partial outputs, cost-balanced mode
 
 struct Layout {
@@ -293,8 +293,10 @@ Views views_of(const fp2_params_t* p, void* ws) {
   v.plan.part_ml = l.part_ml ? (float*)(base + l.part_ml) : nullptr;
   v.plan.cap_items = l.cap_items;
   v.plan.cap_slots = l.cap_slots;
-  v.plan.target_items = 4 * fp2::device_compute_units();
-  const size_t rpu = (size_t)(p->num_q_heads / p->num_kv_heads) * qtile_of(p);
+  const int g = p->num_q_heads / p->num_kv_heads;
+  v.plan.resident_per_cu = fp2::attend_workgroups_per_cu(g, qtile_of(p));
+  v.plan.resident = fp2::device_compute_units() * v.plan.resident_per_cu;
+  const size_t rpu = (size_t)g * qtile_of(p);
   v.part_o_floats = l.part_o ? (size_t)l.cap_slots * rpu * fp2::kHeadDim : 0;
   return v;
 }

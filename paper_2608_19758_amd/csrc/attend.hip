@@ -8,8 +8,8 @@
 // query heads of the group. The grid is persistent: one 8-wave workgroup per
 // compute unit (its LDS ring admits one), or two 4-wave workgroups on half
 // the ring each, so that every SIMD runs two waves; each takes items from an
-// atomic counter in order of decreasing query block (heaviest first), so the
-// run time of an item never holds up the dispatch of others.
+// atomic counter in the order of the work plan, so the run time of an item
+// never holds up the dispatch of others.
 //
 // The key sequence of a unit is a list of 64-key steps: both halves of every
 // kept block, walked from the last kept index down (Eq. csr), then the pooled
@@ -720,9 +720,9 @@ __global__ __launch_bounds__(64 * W, wgs_per_cu(W, FP8)) void attend_kernel(Prob
   const int tid0 = threadIdx.x;
 
   // Persistent workgroups: items of the plan's table (unit, KV split, row
-  // slice, and the unit's split count and partial slot; decreasing query
-  // block, i.e. heaviest first) are taken in order from a counter; the loop
-  // ends for every wave once the counter passes the last item.
+  // slice, and the unit's split count and partial slot) are taken in order
+  // from a counter; the loop ends for every wave once the counter passes the
+  // last item.
 #pragma unroll 1
   for (;;) {
     if (tid0 == 0) {
@@ -1087,6 +1087,8 @@ hipError_t launch_dt(const Problem& p, const Pooled& pooled, const uint8_t* mask
 }  // namespace
 
 int attend_items_per_unit(int g, int qtile) { return g * qtile / (32 * waves_for(g * qtile)); }
+
+int attend_workgroups_per_cu(int g, int qtile) { return wgs_per_cu(waves_for(g * qtile), 0); }
 
 hipError_t launch_attend(const Problem& p, const Pooled& pooled, const uint8_t* mask,
                          const KeptLists& kl, const Plan& plan, void* out, float* lse,

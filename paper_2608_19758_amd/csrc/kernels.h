@@ -63,9 +63,9 @@ struct KeptLists {
 // Work plan of the attention kernel (Sec. 3.3 Eq. split and Eq. cost), built
 // on the device after the kept lists by plan_kernel. Unit rows are indexed
 // row = (b * Hkv + h) * nbmax + I; the attention order is q = (nbmax - 1 - I)
-// * (batch * Hkv) + b * Hkv + h (decreasing query block, heaviest first).
+// * (batch * Hkv) + b * Hkv + h (decreasing query block).
 struct Plan {
-  int4* items;              // [cap_items] {q, k, U, first partial slot or -1}: unit q in
+  int4* items;              // [cap_items], in the order of the walk: {q, k, U, first partial slot or -1}: unit q in
                             // attention order, split k / wpu, row slice k % wpu, and the
                             // unit's rowinfo entry (so one load describes an item)
   int2* rowinfo;            // [rows] {splits U, first partial slot or -1}
@@ -75,12 +75,16 @@ struct Plan {
                             // value codes for fp8)
   float* part_ml;           // [cap_slots, g * B, 2] {running maximum (base 2), denominator}
   int32_t cap_items, cap_slots;
-  int32_t target_items;     // work items the cost-balanced plan aims at
+  int32_t resident;         // attention workgroups that run at a time
+  int32_t resident_per_cu;  // of them on one compute unit
 };
 
 // Work items of the attention kernel per (sequence, KV head, query block),
 // before splitting: row slices of 32 * waves packed rows.
 int attend_items_per_unit(int g, int qtile);
+
+// Workgroups of the attention kernel that share a compute unit.
+int attend_workgroups_per_cu(int g, int qtile);
 
 // Compute units of the current device (0 if it cannot be queried).
 int device_compute_units();

@@ -6,15 +6,35 @@
 // of 64-key steps (Eq. cost): two per kept block, one per 64 corrected
 // blocks, plus a fixed per-item share. In the cost-balanced mode (splits ==
 // 0) every unit whose cost exceeds a step budget S is cut into
-// U = ceil(cost / S) parts (at most kMaxRowSplits), and S is chosen so that
-// the whole call has about target_items items of at most S steps (never
-// less than kMinSplitSteps, and large enough for the partial-output
-// capacity of the workspace). A fixed count n >= 1 cuts every unit into n.
+// U = ceil(cost / S) parts (at most kMaxRowSplits); S is one resident
+// workgroup's share of the call (never less than a minimum, and large enough
+// for the partial-output capacity of the workspace). A fixed count n >= 1 cuts
+// every unit into n.
 // Part u of a unit walks kept-list positions [u ceil(T/U), min((u+1)
 // ceil(T/U), T)) of its T kept blocks and the u-th of U equal ranges of the
-// pruned blocks (Eq. split). The plan is an item table in attention order
-// (decreasing query block, heaviest first, units without queries left out),
-// per-unit {U, first partial slot}, and the list of units with U > 1.
+// pruned blocks (Eq. split). The plan is an item table by decreasing cost
+// class (units without queries left out), per-unit {U, first partial slot},
+// and the list of units with U > 1.
+//
+// Heaviest first: the attention's workgroups take items in table order, so a
+// heavy item near the end of the table runs on while the others idle. The
+// selected blocks of the heads of one query block differ by up to 20x, so the
+// order of decreasing query block left the chip idle for 40% of a chunked
+// call: an 8K bf16 chunk after 56K tokens 1.42 -> 1.00 ms, four ragged fp8
+// extends 0.94 -> 0.70 ms, a 32K prompt 1.667 -> 1.638 ms. kClasses linear
+// cost classes come within 1% of a full sort; within a class the items keep
+// the order of decreasing query block. Where no unit weighs much
+// against a workgroup's share the order stays that of the query blocks, which
+// mixes heavy and light items on the chip at any time (sorted: 128K fp8 5.20 ->
+// 5.27 ms), and so does it for 4-wave workgroups, two of which share a compute
+// unit and level each other (128-row tiles at 32K 1.03 -> 1.23 ms when
+// sorted). A budget of one share needs the fewest parts that still level the
+// load: a quarter of it costs more in partial outputs.
+//
+// Latency-bound: all of it lies between the selection and the attention. Every
+// workgroup computes all costs (coalesced over the counts, kept in LDS) and
+// the class histogram, and writes the table entries of its own range of
+// units, so no workgroup waits for another.
 //
 // combine_kernel merges the parts of every split unit with the log-sum-exp
 // weights: M = max_u m_u, w_u = 2^(m_u - M), O = c_v sum_u w_u o_u /
@@ -32,200 +52,241 @@ namespace fp2 {
 namespace {
 
 constexpr float kLn2 = 0.69314718055994530942f;
-constexpr int kPlanThreads = 1024;
-constexpr int kPlanWaves = kPlanThreads / 64;
-constexpr int kMinSplitSteps = 16;   // smallest step budget of an item
+constexpr int kPlanThreads = 1024;   // threads of a plan workgroup
+constexpr int kPlanThreadsFew = 256;   // the same for at most kPlanFewUnits units: shorter barriers
+constexpr int kPlanFewUnits = 1024;
+// Smallest step budget of an item: below it the parts' fixed work and partial
+// outputs cost more than they level, unless the call has so few items that
+// most compute units would have none.
+constexpr int kMinSplitSteps = 16;
+constexpr int kMinSplitStepsFew = 8;
 constexpr int kItemSteps = 2;        // fixed per-item cost (query load, set-up), in steps
-constexpr int kMaxRowSplits = 32;    // one part per lane of the combine's half-wave
-constexpr int kCostCache = 16384;    // units whose costs the plan keeps in LDS (64 KiB)
+constexpr int kMaxRowSplits = 64;    // two parts per lane of the combine's half-wave
+constexpr int kClasses = 32;         // cost classes of the item order
+// Items of 8-wave workgroups (one per compute unit) are put in order of cost
+// when the heaviest unit exceeds this part of a workgroup's share of the call.
+// The order of query blocks shares more K/V in the caches, which weighs more
+// in fp8 (10.7K tokens, heaviest 1.24 shares: sorted 254 -> 260 us; bf16 30K,
+// 0.83 shares: 786 -> 767 us).
+constexpr double kSortAboveBf16 = 0.6, kSortAboveFp8 = 1.5;
+constexpr int kCostCache = 32768;    // units whose costs a plan workgroup keeps in LDS (64 KiB)
+constexpr int kPlanUnits = 512;      // units whose entries a plan workgroup writes (at least)
+constexpr int kPlanGroups = 32;      // plan workgroups (at most)
+constexpr uint32_t kNoCost = 0xffffu;  // a unit without queries; real costs are below 2 * 8192 + 131
 
-__device__ double block_sum(double v, double* sh) {
+// Sum of v and maximum of m over the TH threads of the workgroup.
+template <int TH>
+__device__ void block_sum_max(double& v, int& m, double* shd, int* shi) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  for (int o = 32; o > 0; o >>= 1) {
+    v += __shfl_xor(v, o, 64);
+    m = max(m, __shfl_xor(m, o, 64));
+  }
   __syncthreads();
-  if (lane == 0) sh[w] = v;
+  if (lane == 0) {
+    shd[w] = v;
+    shi[w] = m;
+  }
   __syncthreads();
-  double t = 0.0;
-  for (int k = 0; k < kPlanWaves; ++k) t += sh[k];
-  return t;
+  v = 0.0;
+  for (int k = 0; k < TH / 64; ++k) {
+    v += shd[k];
+    m = max(m, shi[k]);
+  }
 }
 
-__device__ int block_max(int v, int* sh) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
-  __syncthreads();
-  if (lane == 0) sh[w] = v;
-  __syncthreads();
-  int t = sh[0];
-  for (int k = 1; k < kPlanWaves; ++k) t = max(t, sh[k]);
-  return t;
+// Cost in steps of one row slice of unit row = (b * Hkv + h) * nbmax + I, or
+// kNoCost without queries.
+__device__ __forceinline__ uint32_t unit_cost(const Problem& p, int cnt, int I, int b) {
+  const int Lq = p.cu[b + 1] - p.cu[b], Lk = p.cuk[b + 1] - p.cuk[b];
+  if (I * p.qtile >= Lq) return kNoCost;
+  const int Ia = (Lk - Lq + min(Lq, (I + 1) * p.qtile) - 1) / kBlock;
+  const int pruned = p.corr ? max(0, Ia + 1 - cnt) : 0;   // at most, below the last block
+  return (uint32_t)(2 * cnt + (pruned + 63) / 64 + kItemSteps);
 }
 
-// Exclusive prefix sum over the workgroup (thread order); `total` is the sum
-// over all threads.
-__device__ int block_excl_scan(int v, int* sh, int& total) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int inc = v;
-  for (int o = 1; o < 64; o <<= 1) {
-    const int t = __shfl_up(inc, o, 64);
-    if (lane >= o) inc += t;
+// Lanes of the wave that are `on` and hold the same key (6 bits) as this one.
+__device__ __forceinline__ uint64_t match_key(int key, bool on) {
+  uint64_t m = __ballot(on);
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    const uint64_t b = __ballot((key >> i) & 1);
+    m &= (key >> i) & 1 ? b : ~b;
   }
-  __syncthreads();
-  if (lane == 63) sh[w] = inc;
-  __syncthreads();
-  int pre = 0;
-  total = 0;
-  for (int k = 0; k < kPlanWaves; ++k) {
-    const int x = sh[k];
-    pre += k < w ? x : 0;
-    total += x;
-  }
-  return pre + inc - v;
+  return m;
 }
 
-// Walk over attention-order indices q = (nbmax - 1 - I) * nbh + bh from a
-// start index: unit row (b * Hkv + h) * nbmax + I, sequence b and query
-// block I, with one division at the start and none per step.
-struct UnitWalk {
-  int I, bh, b, h, nbh, hkv, nbmax;
-  __device__ UnitWalk(const Problem& p, int q0) : nbh(p.batch * p.hkv), hkv(p.hkv), nbmax(p.nbmax) {
-    I = nbmax - 1 - q0 / nbh;
-    bh = q0 % nbh;
-    b = bh / hkv;
-    h = bh - b * hkv;
-  }
-  __device__ int row() const { return bh * nbmax + I; }
-  __device__ void next() {
-    ++bh;
-    if (++h == hkv) {
-      h = 0;
-      ++b;
-    }
-    if (bh == nbh) {
-      bh = b = h = 0;
-      --I;
-    }
-  }
-};
-
-__global__ __launch_bounds__(kPlanThreads) void plan_kernel(Problem p, KeptLists kl, Plan plan,
+// Units are indexed in attention order q = (nbmax - 1 - I) * nbh + bh, unit row
+// bh * nbmax + I. Workgroup g of gridDim.x writes the entries of units
+// [g * chunk, (g + 1) * chunk).
+template <int TH>
+__global__ __launch_bounds__(TH) void plan_kernel(Problem p, KeptLists kl, Plan plan,
                                                             int wpu) {
-  __shared__ double shd[kPlanWaves];
-  __shared__ int shi[kPlanWaves];
-  __shared__ int sc[kCostCache];
+  constexpr int kWaves = TH / 64;
+  __shared__ double shd[kWaves];
+  __shared__ int shi[kWaves];
+  __shared__ uint16_t sc[kCostCache];
+  // items per class of unsplit and of split units: all of them, and those of
+  // earlier workgroups' units; a class's table entries are those of its split
+  // units, then the unsplit ones in attention order
+  __shared__ int hist[4 * kClasses];
+  __shared__ int pos[2 * kClasses];    // next entries of a class for this workgroup: unsplit, split
+  __shared__ int wtot[kWaves][kClasses];
+  __shared__ int next[2];              // next partial slot and split-list entry
   const int tid = threadIdx.x;
   const int nbh = p.batch * p.hkv;
   const int R = nbh * p.nbmax;
-  // thread tid owns the attention-order indices q in [q0, q1): contiguous, so
-  // one scan over the threads orders the whole table
-  const int per = (R + kPlanThreads - 1) / kPlanThreads;
-  const int q0 = min(R, tid * per), q1 = min(R, q0 + per);
-
-  // cost in steps of one row slice of every unit with queries (-1: none),
-  // kept in LDS when the table is small enough (indexed by q), else in
-  // rowinfo.x until the plan overwrites it
+  const int chunk = (R + (int)gridDim.x - 1) / (int)gridDim.x;
+  const int q0 = min(R, (int)blockIdx.x * chunk), q1 = min(R, q0 + chunk);
   const bool in_lds = R <= kCostCache;
-  auto cost_at = [&](int q, int row) -> int { return in_lds ? sc[q] : plan.rowinfo[row].x; };
+  auto cost_of = [&](int q) -> uint32_t {
+    if (in_lds) return sc[q];
+    const int I = p.nbmax - 1 - q / nbh, bh = q % nbh;
+    return unit_cost(p, kl.cnt[bh * p.nbmax + I], I, bh / p.hkv);
+  };
+
+  // costs, read in the order of the rows (coalesced), four rows in flight
   double tot = 0.0;
   int mx = 0;
-  // eight units at a time: their loads are issued together
-  UnitWalk u(p, q0);
-  for (int qb = q0; qb < q1; qb += 8) {
-    int row[8], I[8], b[8], cnt[8], lq[8], lk[8];
+  for (int r0 = tid; r0 < R; r0 += 4 * TH) {
+    int cnt[4];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      row[j] = u.row();
-      I[j] = u.I;
-      b[j] = u.b;
-      u.next();
+    for (int j = 0; j < 4; ++j) {
+      const int row = r0 + j * TH;
+      cnt[j] = row < R ? kl.cnt[row] : 0;
     }
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const bool v = qb + j < q1;
-      cnt[j] = v ? kl.cnt[row[j]] : 0;
-      lq[j] = v ? p.cu[b[j] + 1] - p.cu[b[j]] : 0;
-      lk[j] = v ? p.cuk[b[j] + 1] - p.cuk[b[j]] : 0;
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      if (qb + j >= q1) break;
-      const int Lq = lq[j];
-      int cost = -1;
-      if (I[j] * p.qtile < Lq) {
-        const int Ia = (lk[j] - Lq + min(Lq, (I[j] + 1) * p.qtile) - 1) / kBlock;
-        const int pruned = p.corr ? max(0, Ia + 1 - cnt[j]) : 0;   // at most, below the last block
-        cost = 2 * cnt[j] + (pruned + 63) / 64 + kItemSteps;
-        tot += (double)cost * wpu;
-        mx = max(mx, cost);
+    for (int j = 0; j < 4; ++j) {
+      const int row = r0 + j * TH;
+      if (row >= R) break;
+      const int bh = row / p.nbmax, I = row - bh * p.nbmax;
+      const uint32_t c = unit_cost(p, cnt[j], I, bh / p.hkv);
+      if (c != kNoCost) {
+        tot += (double)c * wpu;
+        mx = max(mx, (int)c);
       }
-      if (in_lds)
-        sc[qb + j] = cost;
-      else
-        plan.rowinfo[row[j]] = make_int2(cost, -1);
+      if (in_lds) sc[(p.nbmax - 1 - I) * nbh + bh] = (uint16_t)c;
     }
   }
-  tot = block_sum(tot, shd);   // (its barriers also publish sc)
-  mx = block_max(mx, shi);
+  if (tid < 4 * kClasses) hist[tid] = 0;
+  if (tid < 2) next[tid] = 0;
+  block_sum_max<TH>(tot, mx, shd, shi);   // (its barriers also publish sc)
+
+  // one resident workgroup's share of the call's steps
+  const double share = tot / (double)max(1, plan.resident);
+  const bool sorted = plan.resident_per_cu == 1 && (double)mx > (p.fp8 ? kSortAboveFp8 : kSortAboveBf16) * share;
 
   // step budget of the cost-balanced mode
   int S = 0;
   if (p.splits == 0) {
-    S = max(kMinSplitSteps, (int)ceil(tot / (double)max(1, plan.target_items)));
+    const bool few = (int64_t)R * wpu * 16 <= plan.resident;
+    S = max(few ? kMinSplitStepsFew : kMinSplitSteps, (int)ceil(share));
     while (S < mx) {   // grow S until the parts fit the partial-output slots
-      int need = 0;
-      UnitWalk w(p, q0);
-      for (int q = q0; q < q1; ++q, w.next()) {
-        const int cost = cost_at(q, w.row());
-        if (cost > S) need += min(kMaxRowSplits, (cost + S - 1) / S);
+      double need = 0.0;
+      int none = 0;
+      for (int q = tid; q < R; q += TH) {
+        const uint32_t c = cost_of(q);
+        if (c != kNoCost && (int)c > S) need += min(kMaxRowSplits, ((int)c + S - 1) / S);
       }
-      need = (int)block_sum((double)need, shd);
-      if (need <= plan.cap_slots) break;
-      S *= 2;
+      block_sum_max<TH>(need, none, shd, shi);
+      if (need <= (double)plan.cap_slots) break;
+      S = max(S + max(1, S / 4), (int)((double)S * need / (double)max(1, plan.cap_slots)));
     }
   }
-  auto parts = [&](int cost) -> int {
-    if (cost < 0) return 0;
+  auto parts = [&](uint32_t c) -> int {
+    if (c == kNoCost) return 0;
     if (p.splits > 0) return p.splits;
-    return cost > S ? min(kMaxRowSplits, (cost + S - 1) / S) : 1;
+    return (int)c > S ? min(kMaxRowSplits, ((int)c + S - 1) / S) : 1;
+  };
+  // class of a unit's parts: linear in their cost, 0 the heaviest
+  const int top = p.splits > 0 ? (mx + p.splits - 1) / p.splits
+                               : max(min(mx, S), (mx + kMaxRowSplits - 1) / kMaxRowSplits);
+  auto class_of = [&](uint32_t c, int U) -> int {
+    if (!sorted) return 0;
+    const int pc = min(top, ((int)c + U - 1) / U);
+    return kClasses - 1 - (int)((uint32_t)pc * kClasses / (uint32_t)(top + 1));
   };
 
-  // items in attention order, partial slots and split units: this thread's
-  // totals, their exclusive scans over the threads, then the entries
-  int ni = 0, ns = 0, nsr = 0;
-  {
-    UnitWalk w(p, q0);
-    for (int q = q0; q < q1; ++q, w.next()) {
-      const int U = parts(cost_at(q, w.row()));
-      ni += U * wpu;
-      ns += U > 1 ? U : 0;
-      nsr += U > 1 ? 1 : 0;
+  // items per class, of all units and of those before q0; partial slots and
+  // split units before q0 (units of one part by ballots, the others one by one)
+  for (int qb = 0; qb < R; qb += TH) {
+    const int q = qb + tid;
+    const uint32_t c = q < R ? cost_of(q) : kNoCost;
+    const int U = parts(c);
+    const int cl = U > 0 ? class_of(c, U) : 0;
+    const bool before = q < q0;
+    const uint64_t m = match_key(cl | (before ? kClasses : 0), U == 1);
+    if (U == 1 && (m & ((1ull << (tid & 63)) - 1ull)) == 0) {
+      const int n = __popcll(m) * wpu;
+      atomicAdd(&hist[cl], n);
+      if (before) atomicAdd(&hist[kClasses + cl], n);
+    } else if (U > 1) {
+      atomicAdd(&hist[2 * kClasses + cl], U * wpu);
+      if (before) {
+        atomicAdd(&hist[3 * kClasses + cl], U * wpu);
+        atomicAdd(&next[0], U);
+        atomicAdd(&next[1], 1);
+      }
     }
   }
-  int ti, ts, tsr;
-  int bi = block_excl_scan(ni, shi, ti);
-  int bs = block_excl_scan(ns, shi, ts);
-  int bsr = block_excl_scan(nsr, shi, tsr);
-  UnitWalk w(p, q0);
-  for (int q = q0; q < q1; ++q, w.next()) {
-    const int row = w.row();
-    const int U = parts(cost_at(q, row));
-    if (U == 0) {
-      if (in_lds) plan.rowinfo[row] = make_int2(-1, -1);
-      continue;
-    }
-    const int slot = U > 1 ? bs : -1;
-    plan.rowinfo[row] = make_int2(U, slot);
-    if (U > 1) {
-      plan.splitrows[bsr++] = row;
-      bs += U;
-    }
-    for (int k = 0; k < U * wpu; ++k) plan.items[bi + k] = make_int4(q, k, U, slot);
-    bi += U * wpu;
+  __syncthreads();
+  if (tid < kClasses) {
+    int at = 0;
+    for (int k = 0; k < tid; ++k) at += hist[k] + hist[2 * kClasses + k];
+    pos[kClasses + tid] = at + hist[3 * kClasses + tid];
+    pos[tid] = at + hist[2 * kClasses + tid] + hist[kClasses + tid];
   }
-  if (tid == 0) {
+  __syncthreads();
+
+  // entries of this workgroup's units; an unsplit unit's rank is that among
+  // the lower lanes of the wave, then over the waves in turn
+  const int lane = tid & 63, w = tid >> 6;
+  for (int qb = q0; qb < q1; qb += TH) {
+    const int q = qb + tid;
+    const uint32_t c = q < q1 ? cost_of(q) : kNoCost;
+    const int U = parts(c);
+    const int cl = U > 0 ? class_of(c, U) : 0;
+    const uint64_t m = match_key(cl, U == 1);
+    const int rank = __popcll(m & ((1ull << lane) - 1ull));
+    if (tid < kClasses) {
+#pragma unroll
+      for (int v = 0; v < kWaves; ++v) wtot[v][tid] = 0;
+    }
+    __syncthreads();
+    if (U == 1 && (m >> lane) == 1) wtot[w][cl] = (rank + 1) * wpu;   // the class's last lane
+    __syncthreads();
+    if (tid < kClasses) {
+      int at = pos[tid];
+#pragma unroll
+      for (int v = 0; v < kWaves; ++v) {
+        const int n = wtot[v][tid];
+        wtot[v][tid] = at;
+        at += n;
+      }
+      pos[tid] = at;
+    }
+    __syncthreads();
+    if (q < q1) {
+      const int row = (q % nbh) * p.nbmax + (p.nbmax - 1 - q / nbh);
+      int slot = -1, at = wtot[w][cl] + rank * wpu;
+      if (U > 1) {
+        at = atomicAdd(&pos[kClasses + cl], U * wpu);
+        slot = atomicAdd(&next[0], U);
+        plan.splitrows[atomicAdd(&next[1], 1)] = row;
+      }
+      plan.rowinfo[row] = U > 0 ? make_int2(U, slot) : make_int2(-1, -1);
+      for (int k = 0; k < U * wpu; ++k) plan.items[at + k] = make_int4(q, k, U, slot);
+    }
+    __syncthreads();
+  }
+  // (the last workgroup's running totals end at the call's)
+  __syncthreads();
+  if (blockIdx.x == gridDim.x - 1 && tid == 0) {
+    int ti = 0;
+    for (int k = 0; k < kClasses; ++k) ti += hist[k] + hist[2 * kClasses + k];
     plan.counts[0] = 0;
     plan.counts[1] = ti;
-    plan.counts[2] = tsr;
+    plan.counts[2] = next[1];
   }
 }
 
@@ -249,17 +310,25 @@ __global__ __launch_bounds__(256) void combine_kernel(Problem p, Plan plan,
     const int pr = grp * 8 + sub;              // packed row of this half-wave
     const int pos = I * p.qtile + pr / G;
     if (pos >= p.cu[b + 1] - p.cu[b]) continue;
-    // lane u < U holds part u's {m, l}
-    float m = -INFINITY, l = 0.f;
-    if (lane < U) {
-      const float2 ml = *(const float2*)(plan.part_ml + 2 * ((int64_t)(slot0 + lane) * rpu + pr));
-      m = ml.x;
-      l = ml.y;
+    // lane u holds {m, l} of parts u and u + 32
+    float m[2], l[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      m[k] = -INFINITY;
+      l[k] = 0.f;
+      if (lane + 32 * k < U) {
+        const float2 ml =
+            *(const float2*)(plan.part_ml + 2 * ((int64_t)(slot0 + lane + 32 * k) * rpu + pr));
+        m[k] = ml.x;
+        l[k] = ml.y;
+      }
     }
-    float M = m;
+    float M = fmaxf(m[0], m[1]);
     for (int o = 16; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o, 32));
-    const float wgt = m == -INFINITY ? 0.f : fast_exp2(m - M);
-    float lt = wgt * l;
+    float wgt[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) wgt[k] = m[k] == -INFINITY ? 0.f : fast_exp2(m[k] - M);
+    float lt = wgt[0] * l[0] + wgt[1] * l[1];
     for (int o = 16; o > 0; o >>= 1) lt += __shfl_xor(lt, o, 32);
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int u0 = 0; u0 < U; u0 += 4) {   // four parts' loads in flight at a time
@@ -268,7 +337,7 @@ __global__ __launch_bounds__(256) void combine_kernel(Problem p, Plan plan,
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const int u = u0 + k;
-        wu[k] = __shfl(wgt, u & 31, 32);
+        wu[k] = __shfl(u < 32 ? wgt[0] : wgt[1], u & 31, 32);
         o[k] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (u < U && wu[k] != 0.f)
           o[k] = *(const float4*)(plan.part_o + ((int64_t)(slot0 + u) * rpu + pr) * kHeadDim + c);
@@ -313,7 +382,15 @@ int device_compute_units() {
 
 hipError_t launch_plan(const Problem& p, const KeptLists& kl, const Plan& plan, hipStream_t s) {
   if (p.batch == 0 || p.nbmax == 0) return hipSuccess;
-  plan_kernel<<<1, kPlanThreads, 0, s>>>(p, kl, plan, attend_items_per_unit(p.g, p.qtile));
+  const int64_t units = (int64_t)p.batch * p.hkv * p.nbmax;
+  // past the cost cache every workgroup reads all counts three times: fewer of them
+  const int64_t most = units <= kCostCache ? kPlanGroups : 4;
+  const unsigned grid = (unsigned)std::max<int64_t>(1, std::min(most, units / kPlanUnits));
+  const int wpu = attend_items_per_unit(p.g, p.qtile);
+  if (units <= kPlanFewUnits)
+    plan_kernel<kPlanThreadsFew><<<grid, kPlanThreadsFew, 0, s>>>(p, kl, plan, wpu);
+  else
+    plan_kernel<kPlanThreads><<<grid, kPlanThreads, 0, s>>>(p, kl, plan, wpu);
   return hipGetLastError();
 }
 

@@ -1,0 +1,71 @@
+"""The attention's work plan at the edges of its rules: a unit cut into more
+than 32 parts, cost-ordered items over more than one plan workgroup, and more
+units than the plan keeps costs of in LDS. The plan only decides where and when
+a part runs, so without splits an output equals that of any other call that
+holds the sequence, bit for bit, and with planned splits it equals the unsplit
+one within the output tolerance (parts are merged by their log-sum-exp)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2608_19758_amd as fp2
+import synth
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+
+def _attend(wl, mask, splits):
+    d = gu.device_tensors(wl)
+    p = gu.params_for(wl, 0.5, kv_splits=splits)
+    out, lse = fp2.attend(p, d["q"], d["k_cache"], d["v_cache"], d["cu_seqlens"],
+                          torch.from_numpy(mask).cuda(), d["block_table"],
+                          cu_seqlens_host=wl.cu_seqlens, q_scale=d["q_scale"],
+                          k_scale=d["k_scale"], v_scale=d["v_scale"], want_lse=True,
+                          **gu.kv_args(wl, d))
+    torch.cuda.synchronize()
+    return out.float().cpu().numpy(), lse.cpu().numpy()
+
+
+# (new tokens, prefix, query heads, KV heads): one tail block whose dense head
+# takes 64 parts of some 10 steps; 1280 units in two plan workgroups
+@pytest.mark.parametrize("n,prefix,hq,hkv", [(128, 40960, 8, 2), (20480, 0, 16, 8)])
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+def test_one_dense_head(dtype, n, prefix, hq, hkv):
+    print("case", dtype, n, prefix, hq, hkv, flush=True)
+    wl = synth.generate(synth.Spec("plan", [n], hq, hkv, dtype=dtype, page_size=64, seed=5,
+                                   prefix=[prefix] if prefix else None))
+    nq, nk = (n + 127) // 128, (n + prefix + 127) // 128
+    last = prefix // 128 + np.arange(nq)[:, None]
+    j = np.arange(nk)[None, :]
+    mask = np.zeros((1, hkv, nq, nk), np.uint8)
+    mask[0] = (j == 0) | ((j <= last) & (j > last - 2))
+    mask[0, 1] = j <= last                        # the dense head
+    o1, l1 = _attend(wl, mask, 1)
+    o0, l0 = _attend(wl, mask, 0)
+    print("planned against unsplit: out %.3g, lse %.3g" % (np.abs(o0 - o1).max(), np.abs(l0 - l1).max()))
+    assert np.isfinite(o1).all() and np.abs(o1).max() > 0
+    assert np.abs(o0 - o1).max() <= gu.TOL[dtype]
+    assert np.abs(l0 - l1).max() <= gu.LSE_TOL[dtype]
+
+
+def test_more_units_than_cached_costs():
+    """33 sequences bounded by 16500 tokens and 8 KV heads make 34056 units (the
+    plan keeps 32768 costs): the rows of the longest and of a short sequence
+    equal those of calls that hold it alone."""
+    lens = [16500] + [40] * 32
+    wl = synth.generate(synth.Spec("plan_many", lens, 8, 8, page_size=0, seed=6))
+    alpha = 0.99
+    out, _, lse = gu.gpu_prefill(wl, gu.params_for(wl, alpha, kv_splits=1, score_splits=1))
+    d = gu.device_tensors(wl)
+    for b in (0, 32):
+        r0, r1 = int(wl.cu_seqlens[b]), int(wl.cu_seqlens[b + 1])
+        cu = np.array([0, r1 - r0], np.int32)
+        p = fp2.make_params(batch=1, num_q_heads=8, num_kv_heads=8, max_seq_len=r1 - r0, alpha=alpha,
+                            sink_blocks=1, window_blocks=2, kv_splits=1, score_splits=1)
+        o, _, l = fp2.prefill(p, d["q"][r0:r1].contiguous(), d["k_cache"][r0:r1].contiguous(),
+                              d["v_cache"][r0:r1].contiguous(), torch.from_numpy(cu).cuda(),
+                              cu_seqlens_host=cu, want_lse=True)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(o.float().cpu().numpy(), out[r0:r1])
+        np.testing.assert_array_equal(l.cpu().numpy(), lse[r0:r1])
