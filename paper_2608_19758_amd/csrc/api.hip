@@ -293,10 +293,7 @@ Views views_of(const fp2_params_t* p, void* ws) {
   v.plan.part_ml = l.part_ml ? (float*)(base + l.part_ml) : nullptr;
   v.plan.cap_items = l.cap_items;
   v.plan.cap_slots = l.cap_slots;
-  const int g = p->num_q_heads / p->num_kv_heads;
-  v.plan.resident_per_cu = fp2::attend_workgroups_per_cu(g, qtile_of(p));
-  v.plan.resident = fp2::device_compute_units() * v.plan.resident_per_cu;
-  const size_t rpu = (size_t)g * qtile_of(p);
+  const size_t rpu = (size_t)(p->num_q_heads / p->num_kv_heads) * qtile_of(p);
   v.part_o_floats = l.part_o ? (size_t)l.cap_slots * rpu * fp2::kHeadDim : 0;
   return v;
 }
@@ -348,7 +345,8 @@ fp2_status_t prefill_impl(const fp2_params_t* params, const void* q, const int32
                          params->page_size > 0 ? (params->page_size + fp2::kBlock - 1) / fp2::kBlock
                                                : 0};
   }
-  const Views vw = views_of(params, workspace);
+  Views vw = views_of(params, workspace);
+  fp2::attend_shape(pr, vw.plan);
   hipStream_t s = (hipStream_t)stream;
   const KernelEvents ev = g_events;
   hipError_t e = record(ev.est_begin, s);
@@ -455,7 +453,8 @@ fp2_status_t fp2_attend(const fp2_params_t* params, const void* q, const int32_t
   if ((st = validate_ws(params, workspace, workspace_bytes)) != FP2_OK) return st;
   const fp2::Problem pr = make_problem(params, q, cu_seqlens, cu_seqlens_k, k_cache, v_cache,
                                        block_table, q_scale, k_scale, v_scale);
-  const Views vw = views_of(params, workspace);
+  Views vw = views_of(params, workspace);
+  fp2::attend_shape(pr, vw.plan);
   hipStream_t s = (hipStream_t)stream;
   hipError_t e = hipSuccess;
   if (params->mean_correction) e = fp2::launch_pool(pr, vw.pooled, s);

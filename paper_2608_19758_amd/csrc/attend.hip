@@ -1079,7 +1079,7 @@ template <int FP8>
 hipError_t launch_dt(const Problem& p, const Pooled& pooled, const uint8_t* mask,
                      const KeptLists& kl, const Plan& plan, void* out, float* lse,
                      hipStream_t s) {
-  if (p.g * p.qtile < 256)
+  if (plan.wpu == p.g * p.qtile / 128)
     return launch_cfg<FP8, waves_for(128), 1>(p, pooled, mask, kl, plan, out, lse, s);
   return launch_cfg<FP8, ATT_W, 1>(p, pooled, mask, kl, plan, out, lse, s);
 }
@@ -1088,7 +1088,26 @@ hipError_t launch_dt(const Problem& p, const Pooled& pooled, const uint8_t* mask
 
 int attend_items_per_unit(int g, int qtile) { return g * qtile / (32 * waves_for(g * qtile)); }
 
-int attend_workgroups_per_cu(int g, int qtile) { return wgs_per_cu(waves_for(g * qtile), 0); }
+// 4-wave items for 128-row tiles, and for calls whose 8-wave items would
+// leave three quarters of the compute units without one: a step of a 4-wave
+// item takes about half as long (one wave per SIMD), and the rows of a unit
+// spread over twice the compute units without partial outputs (2K tokens, 4/1
+// heads 54 -> 47 us, 128 bf16 tokens after 421 48.6 -> 43.5 us). With more items
+// the 8-wave ones, which stage each K/V tile for twice the rows, are as fast
+// (at half of the compute units: 3.9K + 512 tokens, 4/1 heads 54.7 us against
+// 57.1; 1.4K fp8 tokens after 82K, 16/8 heads 92 us against 94).
+void attend_shape(const Problem& p, Plan& plan) {
+  const int rows = p.g * p.qtile, cus = device_compute_units();
+  const int64_t units = (int64_t)p.batch * p.hkv * p.nbmax;
+  plan.wpu = attend_items_per_unit(p.g, p.qtile);
+  const int64_t fit = plan.cap_items / (rows / 128);   // units and parts the table holds at 128 rows
+  if (units * plan.wpu * 4 <= cus && p.splits <= 1 && fit >= units) {
+    plan.wpu = rows / 128;
+    plan.cap_slots = (int32_t)std::min<int64_t>(plan.cap_slots, fit - units);
+  }
+  plan.resident_per_cu = wgs_per_cu(rows / (32 * plan.wpu), 0);
+  plan.resident = cus * plan.resident_per_cu;
+}
 
 hipError_t launch_attend(const Problem& p, const Pooled& pooled, const uint8_t* mask,
                          const KeptLists& kl, const Plan& plan, void* out, float* lse,

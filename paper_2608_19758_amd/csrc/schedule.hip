@@ -386,7 +386,7 @@ hipError_t launch_plan(const Problem& p, const KeptLists& kl, const Plan& plan, 
   // past the cost cache every workgroup reads all counts three times: fewer of them
   const int64_t most = units <= kCostCache ? kPlanGroups : 4;
   const unsigned grid = (unsigned)std::max<int64_t>(1, std::min(most, units / kPlanUnits));
-  const int wpu = attend_items_per_unit(p.g, p.qtile);
+  const int wpu = plan.wpu;
   if (units <= kPlanFewUnits)
     plan_kernel<kPlanThreadsFew><<<grid, kPlanThreadsFew, 0, s>>>(p, kl, plan, wpu);
   else

@@ -49,6 +49,33 @@ def test_one_dense_head(dtype, n, prefix, hq, hkv):
     assert np.abs(l0 - l1).max() <= gu.LSE_TOL[dtype]
 
 
+# a call whose units fill at most a quarter of the compute units runs its rows
+# in 128-row items, the longer one in 256-row items: g = 2, 4 and 8, the last
+# query block partial
+@pytest.mark.parametrize("hq,hkv", [(4, 2), (4, 1), (8, 1)])
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+@pytest.mark.parametrize("n", [130, 1000])
+def test_few_units_take_narrow_items(dtype, hq, hkv, n):
+    print("case", dtype, hq, hkv, n, flush=True)
+    wl = synth.generate(synth.Spec("plan_few", [n], hq, hkv, dtype=dtype, page_size=64, seed=8))
+    alpha = 0.99
+    out, mask, lse = gu.gpu_prefill(wl, gu.params_for(wl, alpha, kv_splits=1, score_splits=1))
+    d = gu.device_tensors(wl)
+    # the same sequence in a batch bounded by many more units
+    b = 128 * 4 // hkv
+    cu = np.minimum(np.arange(b + 1), 1).astype(np.int32) * n
+    p = gu.params_for(wl, alpha, kv_splits=1, score_splits=1)
+    p.batch = b
+    table = d["block_table"].repeat(b, 1).contiguous()
+    o, m, l = fp2.prefill(p, d["q"], d["k_cache"], d["v_cache"], torch.from_numpy(cu).cuda(), table,
+                          cu_seqlens_host=cu, q_scale=d["q_scale"], k_scale=d["k_scale"],
+                          v_scale=d["v_scale"], want_lse=True)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(m.cpu().numpy()[:1], mask)
+    np.testing.assert_array_equal(o.float().cpu().numpy(), out)
+    np.testing.assert_array_equal(l.cpu().numpy(), lse)
+
+
 def test_more_units_than_cached_costs():
     """33 sequences bounded by 16500 tokens and 8 KV heads make 34056 units (the
     plan keeps 32768 costs): the rows of the longest and of a short sequence
