@@ -22,6 +22,8 @@
 // from a means cache give the same codes. With a caller's means cache (chunked prefill), complete
 // blocks it already holds are copied from it (512 bytes per block and head
 // instead of the block's K/V), and every block pooled here is written to it.
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace fp2 {
@@ -46,23 +48,32 @@ __device__ __forceinline__ int64_t cache_offset(const Problem& p, const MeansCac
   return (slot * p.hkv + h) * kHeadDim;
 }
 
+// e4m3 code of a bf16 mean (|mean / scale| <= 448).
+__device__ __forceinline__ uint32_t code_of(uint16_t mean, float scale) {
+  const float c = __uint_as_float((uint32_t)mean << 16) / scale;
+  return __builtin_amdgcn_cvt_pk_fp8_f32(fminf(fmaxf(c, -448.f), 448.f), 0.f, 0, false) & 0xFF;
+}
+
+// Leading blocks of sequence b (L KV tokens) that the caller's cache holds.
+__device__ __forceinline__ int cached_blocks(const MeansCache& mc, int b, int L) {
+  return max(0, min(mc.pooled[b], L / kBlock));
+}
+
+// Means of one block (zero past the sequence) by a workgroup; also to the
+// block's slot of a caller's cache.
 template <int FP8>
-__global__ __launch_bounds__(kThreads) void pool_kernel(Problem p, Pooled out, MeansCache mc) {
-  const int J = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+__device__ __forceinline__ void pool_block(const Problem& p, const Pooled& out, const MeansCache& mc,
+                                           int J, int h, int b) {
   const int tid = threadIdx.x;
   const int64_t tok0 = p.cuk[b];
   const int L = p.cuk[b + 1] - (int)tok0;     // KV tokens, a prefix included
   const int64_t obase = (((int64_t)b * p.hkv + h) * p.nbk + J) * kHeadDim;
   const int n = (L + kBlock - 1) / kBlock;
-  // fp8: the e4m3 code means, from the bf16 means (|mean code| <= 448)
+  // fp8: the e4m3 code means, from the bf16 means
   auto store8 = [&](uint16_t kh, uint16_t vb) {
     if (FP8 && out.khat8) {
-      const float kc = __uint_as_float((uint32_t)kh << 16) / p.k_scale[h];
-      const float vc = __uint_as_float((uint32_t)vb << 16) / p.v_scale[h];
-      out.khat8[obase + tid] = (uint8_t)(__builtin_amdgcn_cvt_pk_fp8_f32(
-                                             fminf(fmaxf(kc, -448.f), 448.f), 0.f, 0, false) & 0xFF);
-      out.vbar8[obase + tid] = (uint8_t)(__builtin_amdgcn_cvt_pk_fp8_f32(
-                                             fminf(fmaxf(vc, -448.f), 448.f), 0.f, 0, false) & 0xFF);
+      out.khat8[obase + tid] = (uint8_t)code_of(kh, p.k_scale[h]);
+      out.vbar8[obase + tid] = (uint8_t)code_of(vb, p.v_scale[h]);
     }
   };
   if (J >= n) {
@@ -74,15 +85,6 @@ __global__ __launch_bounds__(kThreads) void pool_kernel(Problem p, Pooled out, M
     return;
   }
   const int64_t cbase = mc.khat ? cache_offset(p, mc, b, J, h) : 0;
-  if (mc.khat && J < min(mc.pooled[b], L / kBlock)) {   // complete block, already pooled
-    if (tid < kHeadDim) {
-      const uint16_t kh = mc.khat[cbase + tid], vb = mc.vbar[cbase + tid];
-      out.khat[obase + tid] = kh;
-      out.vbar[obase + tid] = vb;
-      store8(kh, vb);
-    }
-    return;
-  }
   // the means go to the workspace and, with a cache, to the block's slot
   auto store = [&](uint16_t kh, uint16_t vb) {
     out.khat[obase + tid] = kh;
@@ -224,15 +226,81 @@ __global__ __launch_bounds__(kThreads) void pool_kernel(Problem p, Pooled out, M
   }
 }
 
+template <int FP8>
+__global__ __launch_bounds__(kThreads) void pool_kernel(Problem p, Pooled out) {
+  pool_block<FP8>(p, out, MeansCache{nullptr, nullptr, nullptr, 0}, blockIdx.x, blockIdx.y, blockIdx.z);
+}
+
+// With a caller's cache: the first `copiers` workgroups of a (sequence, KV
+// head) copy the cached means and zero the blocks past the sequence,
+// kCopyBlocks blocks each with 16-byte accesses, and the others pool the
+// uncached blocks, in strides of their number (the host sizes it to the call's
+// new tokens). One workgroup per block, which for a short extend was almost
+// only copies of 512 bytes, took 14.0 us for 128 fp8 tokens after 131K; this
+// takes 8.2 (an 8K bf16 chunk after 56K 16.4 -> 12.2, four fp8 extends 36 -> 29).
+constexpr int kCopyBlocks = 16;
+
+template <int FP8>
+__global__ __launch_bounds__(kThreads) void pool_cached_kernel(Problem p, Pooled out, MeansCache mc,
+                                                               int copiers) {
+  const int x = blockIdx.x, h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
+  const int L = p.cuk[b + 1] - p.cuk[b];
+  const int held = cached_blocks(mc, b, L), n = (L + kBlock - 1) / kBlock;
+  if (x < copiers) {
+    const int J = x * kCopyBlocks + tid / 16, c = tid % 16 * 8;
+    if (J >= p.nbk || (J >= held && J < n)) return;
+    const int64_t ob = (((int64_t)b * p.hkv + h) * p.nbk + J) * kHeadDim + c;
+    uint4 kh = make_uint4(0, 0, 0, 0), vb = kh;   // past the sequence
+    if (J < held) {
+      const int64_t cb = cache_offset(p, mc, b, J, h) + c;
+      kh = *(const uint4*)(mc.khat + cb);
+      vb = *(const uint4*)(mc.vbar + cb);
+    }
+    *(uint4*)(out.khat + ob) = kh;
+    *(uint4*)(out.vbar + ob) = vb;
+    if (FP8 && out.khat8) {
+      auto codes = [](const uint4& m, float scale) -> uint2 {
+        const uint32_t w[4] = {m.x, m.y, m.z, m.w};
+        uint32_t r[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          r[i] = code_of((uint16_t)w[2 * i], scale) | code_of((uint16_t)(w[2 * i] >> 16), scale) << 8 |
+                 code_of((uint16_t)w[2 * i + 1], scale) << 16 |
+                 code_of((uint16_t)(w[2 * i + 1] >> 16), scale) << 24;
+        return make_uint2(r[0], r[1]);
+      };
+      *(uint2*)(out.khat8 + ob) = codes(kh, p.k_scale[h]);
+      *(uint2*)(out.vbar8 + ob) = codes(vb, p.v_scale[h]);
+    }
+    return;
+  }
+  for (int J = held + x - copiers; J < n; J += gridDim.x - copiers) {
+    pool_block<FP8>(p, out, mc, J, h, b);
+    __syncthreads();   // the reduction buffers are free again
+  }
+}
+
 }  // namespace
 
 hipError_t launch_pool(const Problem& p, Pooled out, hipStream_t s, const MeansCache& cache) {
   if (p.batch == 0 || p.nbk == 0) return hipSuccess;
-  dim3 grid(p.nbk, p.hkv, p.batch);
+  if (cache.khat) {
+    // new blocks of a sequence whose prefix is cached: at most its query
+    // blocks and a partial one
+    const int copiers = (p.nbk + kCopyBlocks - 1) / kCopyBlocks;
+    const int fresh = std::min(p.nbk, (p.nbmax * p.qtile + kBlock - 1) / kBlock + 1);
+    const dim3 grid(copiers + fresh, p.hkv, p.batch);
+    if (p.fp8)
+      pool_cached_kernel<1><<<grid, kThreads, 0, s>>>(p, out, cache, copiers);
+    else
+      pool_cached_kernel<0><<<grid, kThreads, 0, s>>>(p, out, cache, copiers);
+    return hipGetLastError();
+  }
+  const dim3 grid(p.nbk, p.hkv, p.batch);
   if (p.fp8)
-    pool_kernel<1><<<grid, kThreads, 0, s>>>(p, out, cache);
+    pool_kernel<1><<<grid, kThreads, 0, s>>>(p, out);
   else
-    pool_kernel<0><<<grid, kThreads, 0, s>>>(p, out, cache);
+    pool_kernel<0><<<grid, kThreads, 0, s>>>(p, out);
   return hipGetLastError();
 }
 

@@ -117,3 +117,28 @@ def test_chunked_with_means_cache(case):
     again = call(wl, d, r2, lens, q2, alpha, cache, [10 ** 6] * len(lens))
     for a, g in zip(want, again):
         np.testing.assert_array_equal(a, g)
+
+
+# cached blocks around the copy group of 16, and far more uncached blocks than
+# the call's new tokens could make; a short and a long sequence
+@pytest.mark.parametrize("held", [0, 3, 15, 16, 17])
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+def test_short_extend_with_partly_filled_cache(dtype, held):
+    print("partly filled", dtype, held, flush=True)
+    lens, q_lens = [2300, 130], [60, 2]
+    wl = synth.generate(spec(lens, 64, dtype=dtype, seed=32))
+    d = gu.device_tensors(wl)
+    alpha = 0.98
+    slots = fp2.means_cache_slots(gu.params_for(wl, alpha), int(wl.num_pages))
+    kh = torch.full((slots, 2, 128), NAN_BF16, dtype=torch.int16, device="cuda")
+    cache = (kh.view(torch.bfloat16), kh.clone().view(torch.bfloat16))
+    rows = [range(L - q, L) for L, q in zip(lens, q_lens)]
+    want = call(wl, d, rows, lens, q_lens, alpha)
+    call(wl, d, rows, lens, q_lens, alpha, cache, [0, 0])    # fills every slot
+    for b in range(2):                                       # and the slots from `held` on are lost
+        for J in range(held, (lens[b] + B - 1) // B):
+            cache[0].view(torch.int16)[slot(wl, b, J)] = NAN_BF16
+            cache[1].view(torch.int16)[slot(wl, b, J)] = NAN_BF16
+    got = call(wl, d, rows, lens, q_lens, alpha, cache, [held, held])
+    for a, g in zip(want, got):
+        np.testing.assert_array_equal(a, g)
