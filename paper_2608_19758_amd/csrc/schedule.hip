@@ -119,6 +119,11 @@ __device__ __forceinline__ uint64_t match_key(int key, bool on) {
 // Units are indexed in attention order q = (nbmax - 1 - I) * nbh + bh, unit row
 // bh * nbmax + I. Workgroup g of gridDim.x writes the entries of units
 // [g * chunk, (g + 1) * chunk).
+// Smallest step budget of the cost-balanced mode for a call of `items` items.
+__host__ __device__ constexpr int min_split_steps(int64_t items, int resident) {
+  return items * 16 <= resident ? kMinSplitStepsFew : kMinSplitSteps;
+}
+
 template <int TH>
 __global__ __launch_bounds__(TH) void plan_kernel(Problem p, KeptLists kl, Plan plan,
                                                             int wpu) {
@@ -179,8 +184,7 @@ __global__ __launch_bounds__(TH) void plan_kernel(Problem p, KeptLists kl, Plan 
   // step budget of the cost-balanced mode
   int S = 0;
   if (p.splits == 0) {
-    const bool few = (int64_t)R * wpu * 16 <= plan.resident;
-    S = max(few ? kMinSplitStepsFew : kMinSplitSteps, (int)ceil(share));
+    S = max(min_split_steps((int64_t)R * wpu, plan.resident), (int)ceil(share));
     while (S < mx) {   // grow S until the parts fit the partial-output slots
       double need = 0.0;
       int none = 0;
@@ -397,6 +401,11 @@ hipError_t launch_plan(const Problem& p, const KeptLists& kl, const Plan& plan, 
 hipError_t launch_combine(const Problem& p, const Plan& plan, void* out, float* lse,
                           hipStream_t s) {
   if (p.batch == 0 || p.nbmax == 0 || plan.cap_slots == 0) return hipSuccess;
+  // Short sequences: even a unit that keeps every key block stays within the
+  // smallest step budget, so nothing is split (4 us of a 43 us call).
+  const int64_t items = (int64_t)p.batch * p.hkv * p.nbmax * plan.wpu;
+  if (p.splits == 0 && 2 * p.nbk + kItemSteps <= min_split_steps(items, plan.resident))
+    return hipSuccess;
   const int64_t bound = (int64_t)(plan.cap_slots / 2) * (p.g * p.qtile / 8);
   const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(bound, 1024));
   if (p.fp8)

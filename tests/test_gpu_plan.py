@@ -76,6 +76,22 @@ def test_few_units_take_narrow_items(dtype, hq, hkv, n):
     np.testing.assert_array_equal(l.cpu().numpy(), lse)
 
 
+# sequences of 3, 7 and 8 key blocks that keep them all, in calls of few and of
+# many items: on both sides of the bounds (8 and 16 steps, two a block and two
+# an item) below which no unit can be split and no merge is launched
+@pytest.mark.parametrize("heads", [1, 32])
+@pytest.mark.parametrize("n", [384, 896, 1024])
+def test_no_merge_below_the_smallest_budget(heads, n):
+    print("case", heads, n, flush=True)
+    wl = synth.generate(synth.Spec("plan_short", [n], heads, heads, page_size=0, seed=9))
+    d = gu.device_tensors(wl)
+    o0, m0, l0 = gu.gpu_prefill(wl, gu.params_for(wl, 0.0), d)
+    o1, m1, l1 = gu.gpu_prefill(wl, gu.params_for(wl, 0.0, kv_splits=1), d)
+    np.testing.assert_array_equal(m0, m1)
+    assert np.isfinite(o0).all() and np.abs(o0 - o1).max() <= gu.TOL["bf16"]
+    assert np.abs(l0 - l1).max() <= gu.LSE_TOL["bf16"]
+
+
 def test_more_units_than_cached_costs():
     """33 sequences bounded by 16500 tokens and 8 KV heads make 34056 units (the
     plan keeps 32768 costs): the rows of the longest and of a short sequence
