@@ -122,15 +122,20 @@ __device__ __forceinline__ void wait_ahead(int ahead) {
 // bytes [base + 16 i, base + 16 i + 16), base taken from M0. Issued as inline
 // assembly so that the compiler does not order every later LDS read behind
 // it; completion is tracked explicitly with wait_vmcnt before the barrier
-// that publishes a stage.
+// that publishes a stage. The hazard recognizer does not look into the
+// assembly either: the copy must not read M0 before one wait state after its
+// scalar write.
 __device__ __forceinline__ void dma16(const void* g, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds)
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds)
                : "memory", "m0");
 }
 
-// The same with a uniform base address and a 32-bit byte offset per lane.
+// The same with a uniform base address and a 32-bit byte offset per lane. The
+// base may come from a vector instruction (readfirstlane, or the reload of a
+// spilled scalar), which a memory instruction must not read before five wait
+// states: the write of M0 and four more, which serve M0 too.
 __device__ __forceinline__ void dma16s(const uint8_t* base, uint32_t off, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds)
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds)
                : "memory", "m0");
 }
 #pragma clang diagnostic pop
