@@ -55,11 +55,12 @@ constexpr float kLn2 = 0.69314718055994530942f;
 constexpr int kPlanThreads = 1024;   // threads of a plan workgroup
 constexpr int kPlanThreadsFew = 256;   // the same for at most kPlanFewUnits units: shorter barriers
 constexpr int kPlanFewUnits = 1024;
-// Smallest step budget of an item: below it the parts' fixed work and partial
-// outputs cost more than they level, unless the call has so few items that
-// most compute units would have none.
+// Smallest step budget of an item: below it the parts' fixed work, partial
+// outputs and merge cost more than the cut saves, also where most compute units
+// have no item (8 there: 40 fp8 tokens after 1500 43.0 -> 45.2 us, 600 with 4/1
+// heads 38.1 -> 41.2, 18 after 500 39.5 -> 42.9; 18 after 1000 47.9 -> 44.8), and
+// every cut rounds fp8 probabilities against one more reference.
 constexpr int kMinSplitSteps = 16;
-constexpr int kMinSplitStepsFew = 8;
 constexpr int kItemSteps = 2;        // fixed per-item cost (query load, set-up), in steps
 constexpr int kMaxRowSplits = 64;    // two parts per lane of the combine's half-wave
 constexpr int kClasses = 32;         // cost classes of the item order
@@ -119,11 +120,6 @@ __device__ __forceinline__ uint64_t match_key(int key, bool on) {
 // Units are indexed in attention order q = (nbmax - 1 - I) * nbh + bh, unit row
 // bh * nbmax + I. Workgroup g of gridDim.x writes the entries of units
 // [g * chunk, (g + 1) * chunk).
-// Smallest step budget of the cost-balanced mode for a call of `items` items.
-__host__ __device__ constexpr int min_split_steps(int64_t items, int resident) {
-  return items * 16 <= resident ? kMinSplitStepsFew : kMinSplitSteps;
-}
-
 template <int TH>
 __global__ __launch_bounds__(TH) void plan_kernel(Problem p, KeptLists kl, Plan plan,
                                                             int wpu) {
@@ -184,7 +180,7 @@ __global__ __launch_bounds__(TH) void plan_kernel(Problem p, KeptLists kl, Plan 
   // step budget of the cost-balanced mode
   int S = 0;
   if (p.splits == 0) {
-    S = max(min_split_steps((int64_t)R * wpu, plan.resident), (int)ceil(share));
+    S = max(kMinSplitSteps, (int)ceil(share));
     while (S < mx) {   // grow S until the parts fit the partial-output slots
       double need = 0.0;
       int none = 0;
@@ -403,9 +399,7 @@ hipError_t launch_combine(const Problem& p, const Plan& plan, void* out, float* 
   if (p.batch == 0 || p.nbmax == 0 || plan.cap_slots == 0) return hipSuccess;
   // Short sequences: even a unit that keeps every key block stays within the
   // smallest step budget, so nothing is split (4 us of a 43 us call).
-  const int64_t items = (int64_t)p.batch * p.hkv * p.nbmax * plan.wpu;
-  if (p.splits == 0 && 2 * p.nbk + kItemSteps <= min_split_steps(items, plan.resident))
-    return hipSuccess;
+  if (p.splits == 0 && 2 * p.nbk + kItemSteps <= kMinSplitSteps) return hipSuccess;
   const int64_t bound = (int64_t)(plan.cap_slots / 2) * (p.g * p.qtile / 8);
   const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(bound, 1024));
   if (p.fp8)
