@@ -56,11 +56,14 @@ constexpr int kPlanThreads = 1024;   // threads of a plan workgroup
 constexpr int kPlanThreadsFew = 256;   // the same for at most kPlanFewUnits units: shorter barriers
 constexpr int kPlanFewUnits = 1024;
 // Smallest step budget of an item: below it the parts' fixed work, partial
-// outputs and merge cost more than the cut saves, also where most compute units
-// have no item (8 there: 40 fp8 tokens after 1500 43.0 -> 45.2 us, 600 with 4/1
-// heads 38.1 -> 41.2, 18 after 500 39.5 -> 42.9; 18 after 1000 47.9 -> 44.8), and
-// every cut rounds fp8 probabilities against one more reference.
+// outputs and merge cost more than the cut saves. bf16 calls whose units would
+// leave most compute units without an entry take 8 (18 tokens after 1000 51 -> 45
+// us, 100 after 60000 98 -> 91, 18 after 500 42 -> 45). fp8 calls do not: their
+// steps are shorter (40 tokens after 1500 43.0 us, cut to 8 steps 45.2; 600 with
+// 4/1 heads 38.1 and 41.2; 18 after 1000 47.9 and 44.8), and every cut rounds
+// their probabilities against one more reference.
 constexpr int kMinSplitSteps = 16;
+constexpr int kMinSplitStepsFewBf16 = 8;
 constexpr int kItemSteps = 2;        // fixed per-item cost (query load, set-up), in steps
 constexpr int kMaxRowSplits = 64;    // two parts per lane of the combine's half-wave
 constexpr int kClasses = 32;         // cost classes of the item order
@@ -115,6 +118,11 @@ __device__ __forceinline__ uint64_t match_key(int key, bool on) {
     m &= (key >> i) & 1 ? b : ~b;
   }
   return m;
+}
+
+// Smallest step budget of the cost-balanced mode for a call of `units` units.
+__host__ __device__ __forceinline__ int min_split_steps(const Problem& p, int64_t units, const Plan& plan) {
+  return !p.fp8 && units * plan.wpu * 16 <= plan.resident ? kMinSplitStepsFewBf16 : kMinSplitSteps;
 }
 
 // Units are indexed in attention order q = (nbmax - 1 - I) * nbh + bh, unit row
@@ -180,7 +188,7 @@ __global__ __launch_bounds__(TH) void plan_kernel(Problem p, KeptLists kl, Plan 
   // step budget of the cost-balanced mode
   int S = 0;
   if (p.splits == 0) {
-    S = max(kMinSplitSteps, (int)ceil(share));
+    S = max(min_split_steps(p, R, plan), (int)ceil(share));
     while (S < mx) {   // grow S until the parts fit the partial-output slots
       double need = 0.0;
       int none = 0;
@@ -399,7 +407,8 @@ hipError_t launch_combine(const Problem& p, const Plan& plan, void* out, float* 
   if (p.batch == 0 || p.nbmax == 0 || plan.cap_slots == 0) return hipSuccess;
   // Short sequences: even a unit that keeps every key block stays within the
   // smallest step budget, so nothing is split (4 us of a 43 us call).
-  if (p.splits == 0 && 2 * p.nbk + kItemSteps <= kMinSplitSteps) return hipSuccess;
+  const int64_t units = (int64_t)p.batch * p.hkv * p.nbmax;
+  if (p.splits == 0 && 2 * p.nbk + kItemSteps <= min_split_steps(p, units, plan)) return hipSuccess;
   const int64_t bound = (int64_t)(plan.cap_slots / 2) * (p.g * p.qtile / 8);
   const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(bound, 1024));
   if (p.fp8)

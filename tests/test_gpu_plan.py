@@ -76,17 +76,19 @@ def test_few_units_take_narrow_items(dtype, hq, hkv, n):
 
 
 # a few tokens whose unit keeps all of its key blocks and takes 2 * blocks + 2
-# steps: whole up to the smallest budget of 16 steps, then in ceil(steps / 16)
-# parts, and with the same numbers as under that fixed count of parts (a call of
-# few items is not cut finer: each cut rounds the fp8 probabilities anew)
+# steps: whole up to the smallest budget (16 steps; 8 in bf16 for calls of so few
+# entries), then in ceil(steps / budget) parts, and with the same numbers as under
+# that fixed count of parts. fp8 units are not cut finer: each cut rounds the
+# probabilities anew.
 @pytest.mark.parametrize("hq,hkv", [(8, 2), (32, 8), (16, 16)])
-@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
-@pytest.mark.parametrize("blocks,parts", [(3, 1), (4, 1), (7, 1), (8, 2), (15, 2), (16, 3)])
-def test_parts_of_a_short_extend(dtype, hq, hkv, blocks, parts):
+@pytest.mark.parametrize("dtype,budget", [("bf16", 8), ("fp8", 16)])
+@pytest.mark.parametrize("blocks", [3, 4, 7, 8, 15, 16])
+def test_parts_of_a_short_extend(dtype, budget, hq, hkv, blocks):
     print("case", dtype, hq, hkv, blocks, flush=True)
     wl = synth.generate(synth.Spec("plan_extend", [18], hq, hkv, dtype=dtype, page_size=64, seed=11,
                                    prefix=[128 * blocks - 40]))
     d = gu.device_tensors(wl)
+    parts = -(-(2 * blocks + 2) // budget)
     o0, m0, l0 = gu.gpu_prefill(wl, gu.params_for(wl, 0.0), d)
     o1, m1, l1 = gu.gpu_prefill(wl, gu.params_for(wl, 0.0, kv_splits=parts), d)
     assert (m0 & 1).sum() == hkv * blocks and np.isfinite(o0).all()
@@ -96,8 +98,8 @@ def test_parts_of_a_short_extend(dtype, hq, hkv, blocks, parts):
 
 
 # sequences of 3, 7 and 8 key blocks that keep them all, in calls of few and of
-# many items: on both sides of the bound (16 steps, two a block and two an item)
-# below which no unit can be split and no merge is launched
+# many entries: on both sides of the bounds (8 and 16 steps, two a block and two
+# an entry) below which no unit can be split and no merge is launched
 @pytest.mark.parametrize("heads", [1, 32])
 @pytest.mark.parametrize("n", [384, 896, 1024])
 def test_no_merge_below_the_smallest_budget(heads, n):
