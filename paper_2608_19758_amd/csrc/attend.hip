@@ -696,44 +696,64 @@ __device__ __forceinline__ void fin_fp8(const uint4* st, Scores<RT>& S, RowState
 
 // Steps 0 .. n-1 of a ring: the scores of a step (qk) then the rest of it
 // (fin). The two waves of a SIMD overlap each other's matrix and vector work.
+// An idle wave only copies.
 template <int W, int FP8, int RT, int RING, int LEAD_SET = 0, class Copier, class QK, class Fin>
-__device__ __forceinline__ void run_steps(uint4* ring, int n, const Copier& cp, QK qk, Fin fin) {
+__device__ __forceinline__ void run_steps(uint4* ring, int n, const Copier& cp, bool idle, QK qk,
+                                          Fin fin) {
   ring_loop<W, FP8, RING, LEAD_SET>(ring, n, cp, [&](const uint4* st, int s) {
+    if (idle) return;
     Scores<RT> S;
     qk(st, S);
     fin(st, S, s);
   });
 }
 
-template <int FP8, int W, int RT>
-__global__ __launch_bounds__(64 * W, wgs_per_cu(W, FP8)) void attend_kernel(Problem p0, Pooled pooled,
-                                                           const uint8_t* __restrict__ mask,
-                                                           KeptLists kl, Plan plan,
-                                                           uint16_t* __restrict__ out,
-                                                           float* __restrict__ lse) {
-  constexpr int RING = ring_u4(W, FP8);
-  __shared__ uint4 ring[RING];
-  __shared__ uint4 aux[kRec];               // kept: copy-address records; correction: pruned list
-  __shared__ int32_t wtot[W];
-  __shared__ int4 s_item;
+// LDS of a workgroup.
+template <int W, int FP8>
+struct Shared {
+  uint4 ring[ring_u4(W, FP8)];
+  uint4 aux[kRec];            // kept: copy-address records; correction: pruned list
+  int32_t wtot[W];
+  int4 item;
+};
 
-  constexpr int M = 32 * RT * W;            // packed rows per work item
+typedef const __attribute__((address_space(4))) Problem KProblem;
+
+// The items a workgroup takes. HALVES: an entry of the plan's table is two
+// items, the halves of its rows, on half of the waves; the others only copy.
+// (FEW, the kernel's, gives each kernel an instance of its own: with one that
+// two kernels share the compiler's register assignment of the bf16 loop is 2%
+// slower.)
+template <int FP8, int W, int RT, bool HALVES, bool FEW>
+__device__ __forceinline__ void attend_items(KProblem* pk0, const Pooled& pooled,
+                                             const uint8_t* __restrict__ mask, const KeptLists& kl,
+                                             const Plan& plan, uint16_t* __restrict__ out,
+                                             float* __restrict__ lse, Shared<W, FP8>& sh) {
+  constexpr int RING = ring_u4(W, FP8);
+  auto& ring = sh.ring;
+  auto& aux = sh.aux;
+  auto& wtot = sh.wtot;
+  auto& s_item = sh.item;
+  constexpr int M = 32 * RT * W;            // packed rows per entry
   // V^T key groups read ahead of the softmax (all four only with a wave per SIMD)
   constexpr int NPRE = W > 4 || wgs_per_cu(W, FP8) > 1 ? 2 : 4;
-  const int wpu = p0.g * p0.qtile / M;      // row slices per unit
-  const int nbh = p0.batch * p0.hkv;
+  const int wpu = pk0->g * pk0->qtile / M;  // row slices per unit
+  const int nbh = pk0->batch * pk0->hkv;
   const int tid0 = threadIdx.x;
 
-  // Persistent workgroups: items of the plan's table (unit, KV split, row
+  // Persistent workgroups: entries of the plan's table (unit, KV split, row
   // slice, and the unit's split count and partial slot) are taken in order
   // from a counter; the loop ends for every wave once the counter passes the
-  // last item.
+  // last one.
 #pragma unroll 1
   for (;;) {
     if (tid0 == 0) {
       const int it = atomicAdd(plan.counts, 1);
       int4 v = make_int4(-1, 0, 0, 0);
-      if (it < plan.counts[1]) v = plan.items[it];
+      if ((it >> HALVES) < plan.counts[1]) {
+        v = plan.items[it >> HALVES];
+        v.z |= (it & HALVES) << 16;   // the item's half, beside the unit's parts
+      }
       s_item = v;
     }
     __syncthreads();
@@ -742,20 +762,18 @@ __global__ __launch_bounds__(64 * W, wgs_per_cu(W, FP8)) void attend_kernel(Prob
     if (cur.x < 0) break;
     // Opaque copies of the thread index and of the argument block: what is
     // derived from them is recomputed per item instead of being held in
-    // registers across the whole loop. p0 is the first kernel argument, so it
-    // sits at offset 0 of the kernel argument segment; its fields are read
-    // back from there with scalar loads.
+    // registers across the whole loop; the fields of the argument block are
+    // read back with scalar loads.
     int tid = tid0;
     asm volatile("" : "+v"(tid));
-    typedef const __attribute__((address_space(4))) Problem KProblem;
-    KProblem* pk = (KProblem*)__builtin_amdgcn_kernarg_segment_ptr();
+    KProblem* pk = pk0;
     asm volatile("" : "+s"(pk));
     KProblem& p = *pk;
 
     const int u = cur.x;                     // attention-order index of the unit
     const int sp = cur.y / wpu;              // its part (KV split) ...
     const int msub = cur.y - sp * wpu;       // ... and row slice
-    const int nsp = cur.z;                   // parts of the unit
+    const int nsp = HALVES ? cur.z & 0xffff : cur.z;   // parts of the unit
     const int I = p.nbmax - 1 - u / nbh;
     const int bh = u % nbh;
     const int b = bh / p.hkv, h = bh % p.hkv;
@@ -776,7 +794,9 @@ __global__ __launch_bounds__(64 * W, wgs_per_cu(W, FP8)) void attend_kernel(Prob
 
     // this lane's query rows (packed rows of Eq. packgqa), one per row tile;
     // G divides 32, so a lane column keeps one query head
-    const int pr0 = msub * M + w * 32 * RT + l32;
+    const bool idle = HALVES && __builtin_amdgcn_readfirstlane(w) >= W / 2;
+    const int wrow = HALVES ? (cur.z >> 16) * (W / 2) + w % (W / 2) : w;
+    const int pr0 = msub * M + wrow * 32 * RT + l32;
     const int hq = h * G + pr0 % G;
     int pos[RT];
     bool qvalid[RT];
@@ -800,7 +820,8 @@ __global__ __launch_bounds__(64 * W, wgs_per_cu(W, FP8)) void attend_kernel(Prob
       const uint8_t* qrow = (const uint8_t*)p.q + qo * (FP8 ? 1 : 2) + (FP8 ? 32 : 16) * half;
 #pragma unroll
       for (int i = 0; i < (FP8 ? 4 : 8); ++i)
-        qraw[rt][i] = *(const uint4*)(qrow + (FP8 ? 64 * (i >> 1) + 16 * (i & 1) : 32 * i));
+        qraw[rt][i] = idle ? make_uint4(0, 0, 0, 0)
+                           : *(const uint4*)(qrow + (FP8 ? 64 * (i >> 1) + 16 * (i & 1) : 32 * i));
     }
 
     RowState<RT> rs;
@@ -929,7 +950,7 @@ __global__ __launch_bounds__(64 * W, wgs_per_cu(W, FP8)) void attend_kernel(Prob
         const KeptCopier<W, FP8, RING> cp(aux, K, V, rph, gshift, rowb, tid);
         if constexpr (FP8) {
           run_steps<W, 1, RT, RING>(
-              ring, nst, cp,
+              ring, nst, cp, idle,
               [&](const uint4* st, Scores<RT>& S) { qk_fp8<RT>(st, qf, S, ol); },
               [&](const uint4* st, Scores<RT>& S, int s) {
                 const int wp = c0 + (s >> 1);   // walk position of the step's block
@@ -938,7 +959,7 @@ __global__ __launch_bounds__(64 * W, wgs_per_cu(W, FP8)) void attend_kernel(Prob
               });
         } else {
           run_steps<W, 0, RT, RING, W == 8 ? 1 : 0>(   // bf16 kept steps: one step ahead
-              ring, nst, cp,
+              ring, nst, cp, idle,
               [&](const uint4* st, Scores<RT>& S) { qk_bf16<RT>(st, qb, S, lane); },
               [&](const uint4* st, Scores<RT>& S, int s) {
                 const int wp = c0 + (s >> 1);   // walk position of the step's block
@@ -996,7 +1017,7 @@ __global__ __launch_bounds__(64 * W, wgs_per_cu(W, FP8)) void attend_kernel(Prob
         const int nst = (np + kStep - 1) / kStep;
         if constexpr (FP8) {
           run_steps<W, 1, RT, RING>(
-              ring, nst, cp,
+              ring, nst, cp, idle,
               [&](const uint4* st, Scores<RT>& S) { qk_fp8<RT>(st, qf, S, ol); },
               [&](const uint4* st, Scores<RT>& S, int s) {
                 const int nv = np - kStep * s;
@@ -1004,7 +1025,7 @@ __global__ __launch_bounds__(64 * W, wgs_per_cu(W, FP8)) void attend_kernel(Prob
               });
         } else {
           run_steps<W, 0, RT, RING>(
-              ring, nst, cp,
+              ring, nst, cp, idle,
               [&](const uint4* st, Scores<RT>& S) { qk_bf16<RT>(st, qb, S, lane); },
               [&](const uint4* st, Scores<RT>& S, int s) {
                 fin_bf16<1, RT, NPRE>(st, S, rs, cs, off, 1.f, 0, pos, false, np - kStep * s,
@@ -1013,6 +1034,8 @@ __global__ __launch_bounds__(64 * W, wgs_per_cu(W, FP8)) void attend_kernel(Prob
         }
       }
     }
+
+    if (idle) continue;   // nothing to write
 
     // fp8: the row sums of P~ from the matrix cores join the denominator
     if constexpr (FP8) {
@@ -1075,15 +1098,44 @@ __global__ __launch_bounds__(64 * W, wgs_per_cu(W, FP8)) void attend_kernel(Prob
   }
 }
 
-template <int FP8, int W, int RT>
+// FEW: a call whose units leave at least half of the workgroups without an
+// entry. Where its plan does so too, an entry is taken as two items: a step takes
+// about half as long with one computing wave per SIMD, and the rows spread over
+// twice the compute units without partial outputs (512 fp8 tokens 44.6 -> 37.5
+// us, 100 + 120 after 60K + 30K with 64/8 heads 71.2 -> 64.5). With more entries
+// whole ones, which stage each K/V tile for twice the rows, are faster (256 after
+// 120K with 64/8 heads 82 us, as halves on two workgroups a compute unit 90).
+// The number of parts is known to the device only, so both loops are in the
+// kernel; the one of all other calls holds the whole entries' alone, which
+// measured 2% faster by itself (32K bf16 1669 -> 1697 us with both).
+template <int FP8, int W, int RT, bool FEW>
+__global__ __launch_bounds__(64 * W, wgs_per_cu(W, FP8)) void attend_kernel(Problem p0, Pooled pooled,
+                                                           const uint8_t* __restrict__ mask,
+                                                           KeptLists kl, Plan plan,
+                                                           uint16_t* __restrict__ out,
+                                                           float* __restrict__ lse) {
+  __shared__ Shared<W, FP8> sh;
+  // p0 is the first kernel argument, so it sits at offset 0 of the kernel
+  // argument segment
+  KProblem* pk = (KProblem*)__builtin_amdgcn_kernarg_segment_ptr();
+  if constexpr (FEW) {
+    if (2 * ld_uniform(plan.counts, 1) <= (int)gridDim.x) {
+      attend_items<FP8, W, RT, true, FEW>(pk, pooled, mask, kl, plan, out, lse, sh);
+      return;
+    }
+  }
+  attend_items<FP8, W, RT, false, FEW>(pk, pooled, mask, kl, plan, out, lse, sh);
+}
+
+template <int FP8, int W, int RT, bool FEW>
 hipError_t launch_cfg(const Problem& p, const Pooled& pooled, const uint8_t* mask,
                       const KeptLists& kl, const Plan& plan, void* out, float* lse,
                       hipStream_t s) {
-  const int cus = device_compute_units();
-  if (cus <= 0) return hipErrorInvalidDevice;
-  const unsigned grid = (unsigned)std::min<int64_t>(plan.cap_items, (int64_t)cus * wgs_per_cu(W, FP8));
-  attend_kernel<FP8, W, RT><<<grid, 64 * W, 0, s>>>(p, pooled, mask, kl, plan,
-                                                          (uint16_t*)out, lse);
+  const int64_t resident = plan.resident;   // each workgroup can take an entry, or half of one
+  const unsigned grid = (unsigned)std::min<int64_t>(plan.cap_items * (FEW ? 2ll : 1ll), resident);
+  if (grid == 0) return hipErrorInvalidDevice;
+  attend_kernel<FP8, W, RT, FEW><<<grid, 64 * W, 0, s>>>(p, pooled, mask, kl, plan,
+                                                               (uint16_t*)out, lse);
   return hipSuccess;
 }
 
@@ -1095,34 +1147,21 @@ template <int FP8>
 hipError_t launch_dt(const Problem& p, const Pooled& pooled, const uint8_t* mask,
                      const KeptLists& kl, const Plan& plan, void* out, float* lse,
                      hipStream_t s) {
-  if (plan.wpu == p.g * p.qtile / 128)
-    return launch_cfg<FP8, waves_for(128), 1>(p, pooled, mask, kl, plan, out, lse, s);
-  return launch_cfg<FP8, ATT_W, 1>(p, pooled, mask, kl, plan, out, lse, s);
+  if (p.g * p.qtile < 256)
+    return launch_cfg<FP8, waves_for(128), 1, false>(p, pooled, mask, kl, plan, out, lse, s);
+  if ((int64_t)p.batch * p.hkv * p.nbmax * plan.wpu * 2 <= plan.resident)
+    return launch_cfg<FP8, ATT_W, 1, true>(p, pooled, mask, kl, plan, out, lse, s);
+  return launch_cfg<FP8, ATT_W, 1, false>(p, pooled, mask, kl, plan, out, lse, s);
 }
 
 }  // namespace
 
 int attend_items_per_unit(int g, int qtile) { return g * qtile / (32 * waves_for(g * qtile)); }
 
-// 4-wave items for 128-row tiles, and for calls whose 8-wave items would
-// leave three quarters of the compute units without one: a step of a 4-wave
-// item takes about half as long (one wave per SIMD), and the rows of a unit
-// spread over twice the compute units without partial outputs (2K tokens, 4/1
-// heads 54 -> 47 us, 128 bf16 tokens after 421 48.6 -> 43.5 us). With more items
-// the 8-wave ones, which stage each K/V tile for twice the rows, are as fast
-// (at half of the compute units: 3.9K + 512 tokens, 4/1 heads 54.7 us against
-// 57.1; 1.4K fp8 tokens after 82K, 16/8 heads 92 us against 94).
 void attend_shape(const Problem& p, Plan& plan) {
-  const int rows = p.g * p.qtile, cus = device_compute_units();
-  const int64_t units = (int64_t)p.batch * p.hkv * p.nbmax;
   plan.wpu = attend_items_per_unit(p.g, p.qtile);
-  const int64_t fit = plan.cap_items / (rows / 128);   // units and parts the table holds at 128 rows
-  if (units * plan.wpu * 4 <= cus && p.splits <= 1 && fit >= units) {
-    plan.wpu = rows / 128;
-    plan.cap_slots = (int32_t)std::min<int64_t>(plan.cap_slots, fit - units);
-  }
-  plan.resident_per_cu = wgs_per_cu(rows / (32 * plan.wpu), 0);
-  plan.resident = cus * plan.resident_per_cu;
+  plan.resident_per_cu = wgs_per_cu(waves_for(p.g * p.qtile), 0);
+  plan.resident = device_compute_units() * plan.resident_per_cu;
 }
 
 hipError_t launch_attend(const Problem& p, const Pooled& pooled, const uint8_t* mask,

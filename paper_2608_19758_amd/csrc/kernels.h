@@ -75,19 +75,16 @@ struct Plan {
                             // value codes for fp8)
   float* part_ml;           // [cap_slots, g * B, 2] {running maximum (base 2), denominator}
   int32_t cap_items, cap_slots;
-  int32_t wpu;              // row slices (items) per unit
+  int32_t wpu;              // row slices (table entries) per unit
   int32_t resident;         // attention workgroups that run at a time
   int32_t resident_per_cu;  // of them on one compute unit
 };
 
 // Work items of the attention kernel per (sequence, KV head, query block),
-// before splitting: row slices of 32 * waves packed rows (the workspace holds
-// that many per unit; a call of few units takes twice as many half as large
-// where its plan fits).
+// before splitting: row slices of 32 * waves packed rows.
 int attend_items_per_unit(int g, int qtile);
 
-// Chooses the item size of a call and fills the plan's wpu, resident and
-// resident_per_cu (and lowers cap_slots to what the item table then holds).
+// Fills the plan's wpu, resident and resident_per_cu.
 void attend_shape(const Problem& p, Plan& plan);
 
 // Compute units of the current device (0 if it cannot be queried).

@@ -49,10 +49,10 @@ def test_one_dense_head(dtype, n, prefix, hq, hkv):
     assert np.abs(l0 - l1).max() <= gu.LSE_TOL[dtype]
 
 
-# a call whose units fill at most a quarter of the compute units runs its rows
-# in 128-row items, one bounded by many more units in 256-row items: g = 2, 4
-# and 8, the last query block partial, at most 3 key blocks so that neither
-# call splits a unit (the default plan)
+# a call whose entries leave half of the workgroups idle takes each as two items
+# of 128 rows, one bounded by many more units as one of 256: g = 2, 4 and 8, the
+# last query block partial, at most 3 key blocks so that neither call splits a
+# unit (the default plan)
 @pytest.mark.parametrize("hq,hkv", [(4, 2), (4, 1), (8, 1)])
 @pytest.mark.parametrize("dtype", ["bf16", "fp8"])
 @pytest.mark.parametrize("n", [130, 380])
@@ -70,6 +70,36 @@ def test_few_units_take_narrow_items(dtype, hq, hkv, n):
                           cu_seqlens_host=cu, q_scale=d["q_scale"], k_scale=d["k_scale"],
                           v_scale=d["v_scale"], want_lse=True)
     torch.cuda.synchronize()
+    np.testing.assert_array_equal(m.cpu().numpy()[:1], mask)
+    np.testing.assert_array_equal(o.float().cpu().numpy(), out)
+    np.testing.assert_array_equal(l.cpu().numpy(), lse)
+
+
+# rows taken as the two halves of an entry (a call whose entries leave half of the
+# workgroups idle) and as whole entries (one bounded by more units) give the same
+# numbers, with and without parts: g = 2, 4 and 8, the last query block partial,
+# a prefix that is not a multiple of the block, pruned blocks corrected
+@pytest.mark.parametrize("hq,hkv", [(4, 2), (4, 1), (8, 1)])
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+@pytest.mark.parametrize("splits", [1, 3])
+def test_half_entries(dtype, hq, hkv, splits):
+    print("case", dtype, hq, hkv, splits, flush=True)
+    wl = synth.generate(synth.Spec("plan_half", [200], hq, hkv, dtype=dtype, page_size=64, seed=12,
+                                   prefix=[1100]))
+    p = gu.params_for(wl, 0.97, kv_splits=splits, score_splits=1)
+    d = gu.device_tensors(wl)
+    out, mask, lse = gu.gpu_prefill(wl, p, d)
+    b = 264 // hkv
+    p.batch = b
+    first = np.minimum(np.arange(b + 1), 1).astype(np.int32)
+    cu, cuk = first * 200, first * 1300
+    o, m, l = fp2.prefill(p, d["q"], d["k_cache"], d["v_cache"], torch.from_numpy(cu).cuda(),
+                          d["block_table"].repeat(b, 1).contiguous(), cu_seqlens_host=cu,
+                          cu_seqlens_k=torch.from_numpy(cuk).cuda(), cu_seqlens_k_host=cuk,
+                          q_scale=d["q_scale"], k_scale=d["k_scale"], v_scale=d["v_scale"],
+                          want_lse=True)
+    torch.cuda.synchronize()
+    assert 0 < (mask & 1).sum() < mask.size
     np.testing.assert_array_equal(m.cpu().numpy()[:1], mask)
     np.testing.assert_array_equal(o.float().cpu().numpy(), out)
     np.testing.assert_array_equal(l.cpu().numpy(), lse)
