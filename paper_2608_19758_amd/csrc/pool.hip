@@ -2,8 +2,9 @@
 // Eq. correction; the block means of Algorithm 1). HBM-bound: every K/V byte of the
 // sequence is read once with 16-byte loads through the page table.
 //
-// One workgroup per (key block J, KV head h, sequence b), 256 threads, over
-// the sequence's KV tokens (a prefix included).
+// A workgroup of 256 threads takes one (key block J, KV head h, sequence b) of
+// the sequence's KV tokens (a prefix included) at a time: one in all without a
+// means cache, the uncached ones in turn with it (pool_cached_kernel).
 //  - bf16: thread (row group rg = tid/16, column chunk c = tid%16) sums tokens
 //    rg, rg+16, ... of the block for columns 8c..8c+7 in fp64. Every bf16
 //    value is exact in fp64 and so are the partial sums of realistic data, so
@@ -19,9 +20,10 @@
 // in fp8 like the kept keys (the pooled statistics quantized as Sec. 4 does
 // under fp8): the kernel also writes the e4m3 code means e4m3(khat / k_scale)
 // and e4m3(vbar / v_scale), derived from the bf16 means so that blocks taken
-// from a means cache give the same codes. With a caller's means cache (chunked prefill), complete
-// blocks it already holds are copied from it (512 bytes per block and head
-// instead of the block's K/V), and every block pooled here is written to it.
+// from a means cache give the same codes. With a caller's means cache (chunked
+// prefill), complete blocks it already holds are copied from it (512 bytes per
+// block and head instead of the block's K/V), and every block pooled here is
+// written to it.
 #include <algorithm>
 
 #include "kernels.h"
@@ -63,8 +65,7 @@ __device__ __forceinline__ int cached_blocks(const MeansCache& mc, int b, int L)
 // block's slot of a caller's cache.
 template <int FP8>
 __device__ __forceinline__ void pool_block(const Problem& p, const Pooled& out, const MeansCache& mc,
-                                           int J, int h, int b) {
-  const int tid = threadIdx.x;
+                                           int J, int h, int b, int tid) {
   const int64_t tok0 = p.cuk[b];
   const int L = p.cuk[b + 1] - (int)tok0;     // KV tokens, a prefix included
   const int64_t obase = (((int64_t)b * p.hkv + h) * p.nbk + J) * kHeadDim;
@@ -228,55 +229,91 @@ __device__ __forceinline__ void pool_block(const Problem& p, const Pooled& out, 
 
 template <int FP8>
 __global__ __launch_bounds__(kThreads) void pool_kernel(Problem p, Pooled out) {
-  pool_block<FP8>(p, out, MeansCache{nullptr, nullptr, nullptr, 0}, blockIdx.x, blockIdx.y, blockIdx.z);
+  pool_block<FP8>(p, out, MeansCache{nullptr, nullptr, nullptr, 0}, blockIdx.x, blockIdx.y, blockIdx.z,
+                  threadIdx.x);
 }
 
-// With a caller's cache: the first `copiers` workgroups of a (sequence, KV
-// head) copy the cached means and zero the blocks past the sequence,
-// kCopyBlocks blocks each with 16-byte accesses, and the others pool the
-// uncached blocks, in strides of their number (the host sizes it to the call's
-// new tokens). One workgroup per block, which for a short extend was almost
-// only copies of 512 bytes, took 14.0 us for 128 fp8 tokens after 131K; this
-// takes 8.2 (an 8K bf16 chunk after 56K 16.4 -> 12.2, four fp8 extends 36 -> 29).
+// With a caller's cache: the first `poolers` workgroups of a KV head share the
+// uncached blocks of all sequences, counted on the device, since the host knows
+// neither how many the cache holds nor in which sequence they are missing; the
+// others copy the cached means and zero the blocks past a sequence, kCopyBlocks
+// blocks each with 16-byte accesses. The poolers fill the chip once over all
+// heads (their registers admit kPoolersBf16 / kPoolersFp8 on a compute unit) and
+// come first: the last workgroups of a grid start some 10 us after the first.
+// One workgroup per block, which for a short extend was almost only copies of 512
+// bytes, took 14.3 us for 128 fp8 tokens after 131K; this takes 9.8 (an 8K bf16
+// chunk after 56K 14.3 -> 13.4, four fp8 extends 31 -> 22). Prefixes the cache does
+// not hold: 57K bf16 42 -> 39 us, 131K fp8 59 -> 68, 100K of one of 16 sequences
+// 138 -> 104, four fp8 extends 137 -> 146; pooled by one workgroup per query block,
+// as if every prefix were cached, these took 1190, 2700, 2730 and 2730.
 constexpr int kCopyBlocks = 16;
+constexpr int kPoolersBf16 = 4, kPoolersFp8 = 5;
 
 template <int FP8>
 __global__ __launch_bounds__(kThreads) void pool_cached_kernel(Problem p, Pooled out, MeansCache mc,
-                                                               int copiers) {
-  const int x = blockIdx.x, h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
-  const int L = p.cuk[b + 1] - p.cuk[b];
-  const int held = cached_blocks(mc, b, L), n = (L + kBlock - 1) / kBlock;
-  if (x < copiers) {
-    const int J = x * kCopyBlocks + tid / 16, c = tid % 16 * 8;
-    if (J >= p.nbk || (J >= held && J < n)) return;
-    const int64_t ob = (((int64_t)b * p.hkv + h) * p.nbk + J) * kHeadDim + c;
-    uint4 kh = make_uint4(0, 0, 0, 0), vb = kh;   // past the sequence
-    if (J < held) {
-      const int64_t cb = cache_offset(p, mc, b, J, h) + c;
-      kh = *(const uint4*)(mc.khat + cb);
-      vb = *(const uint4*)(mc.vbar + cb);
-    }
-    *(uint4*)(out.khat + ob) = kh;
-    *(uint4*)(out.vbar + ob) = vb;
-    if (FP8 && out.khat8) {
-      auto codes = [](const uint4& m, float scale) -> uint2 {
-        const uint32_t w[4] = {m.x, m.y, m.z, m.w};
-        uint32_t r[2];
+                                                               int poolers, int copiers) {
+  const int h = blockIdx.x % p.hkv, i = blockIdx.x / p.hkv, tid = threadIdx.x;
+  if (i >= poolers) {
+    const int tiles = (p.nbk + kCopyBlocks - 1) / kCopyBlocks;   // per sequence
+    for (int64_t k = i - poolers; k < (int64_t)tiles * p.batch; k += copiers) {
+      const int b = (int)(k / tiles), J = (int)(k - (int64_t)b * tiles) * kCopyBlocks + tid / 16;
+      const int c = tid % 16 * 8;
+      const int L = p.cuk[b + 1] - p.cuk[b];
+      const int held = cached_blocks(mc, b, L), n = (L + kBlock - 1) / kBlock;
+      if (J >= p.nbk || (J >= held && J < n)) continue;
+      const int64_t ob = (((int64_t)b * p.hkv + h) * p.nbk + J) * kHeadDim + c;
+      uint4 kh = make_uint4(0, 0, 0, 0), vb = kh;   // past the sequence
+      if (J < held) {
+        const int64_t cb = cache_offset(p, mc, b, J, h) + c;
+        kh = *(const uint4*)(mc.khat + cb);
+        vb = *(const uint4*)(mc.vbar + cb);
+      }
+      *(uint4*)(out.khat + ob) = kh;
+      *(uint4*)(out.vbar + ob) = vb;
+      if (FP8 && out.khat8) {
+        auto codes = [](const uint4& m, float scale) -> uint2 {
+          const uint32_t w[4] = {m.x, m.y, m.z, m.w};
+          uint32_t r[2];
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-          r[i] = code_of((uint16_t)w[2 * i], scale) | code_of((uint16_t)(w[2 * i] >> 16), scale) << 8 |
-                 code_of((uint16_t)w[2 * i + 1], scale) << 16 |
-                 code_of((uint16_t)(w[2 * i + 1] >> 16), scale) << 24;
-        return make_uint2(r[0], r[1]);
-      };
-      *(uint2*)(out.khat8 + ob) = codes(kh, p.k_scale[h]);
-      *(uint2*)(out.vbar8 + ob) = codes(vb, p.v_scale[h]);
+          for (int j = 0; j < 2; ++j)
+            r[j] = code_of((uint16_t)w[2 * j], scale) | code_of((uint16_t)(w[2 * j] >> 16), scale) << 8 |
+                   code_of((uint16_t)w[2 * j + 1], scale) << 16 |
+                   code_of((uint16_t)(w[2 * j + 1] >> 16), scale) << 24;
+          return make_uint2(r[0], r[1]);
+        };
+        *(uint2*)(out.khat8 + ob) = codes(kh, p.k_scale[h]);
+        *(uint2*)(out.vbar8 + ob) = codes(vb, p.v_scale[h]);
+      }
     }
     return;
   }
-  for (int J = held + x - copiers; J < n; J += gridDim.x - copiers) {
-    pool_block<FP8>(p, out, mc, J, h, b);
-    __syncthreads();   // the reduction buffers are free again
+  // this workgroup's share of the head's uncached blocks, sequence after
+  // sequence; lane l of every wave knows sequence b0 + l
+  int t = i, at = 0;
+  for (int b0 = 0; b0 < p.batch; b0 += 64) {
+    const int lane = tid & 63, bl = b0 + lane;
+    int held = 0, fresh = 0;
+    if (bl < p.batch) {
+      const int L = p.cuk[bl + 1] - p.cuk[bl];
+      held = cached_blocks(mc, bl, L);
+      fresh = max(0, min(p.nbk, (L + kBlock - 1) / kBlock) - held);
+    }
+    int upto = fresh;   // uncached blocks of the sequences b0 .. bl
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(upto, o, 64);
+      if (lane >= o) upto += v;
+    }
+    const int first = held - (upto - fresh);   // block of a sequence's share 0 of b0's
+    const int end = at + __builtin_amdgcn_readlane(upto, 63);
+    for (; t < end; t += poolers) {
+      const int l = __ffsll((unsigned long long)__ballot(at + upto > t)) - 1;
+      const int J = t - at + __builtin_amdgcn_readlane(first, l);
+      int tb = tid;   // opaque: what pool_block derives from it is not held across the loop
+      asm volatile("" : "+v"(tb));
+      pool_block<FP8>(p, out, mc, J, h, b0 + l, tb);
+      __syncthreads();   // the reduction buffers are free again
+    }
+    at = end;
   }
 }
 
@@ -285,15 +322,16 @@ __global__ __launch_bounds__(kThreads) void pool_cached_kernel(Problem p, Pooled
 hipError_t launch_pool(const Problem& p, Pooled out, hipStream_t s, const MeansCache& cache) {
   if (p.batch == 0 || p.nbk == 0) return hipSuccess;
   if (cache.khat) {
-    // new blocks of a sequence whose prefix is cached: at most its query
-    // blocks and a partial one
-    const int copiers = (p.nbk + kCopyBlocks - 1) / kCopyBlocks;
-    const int fresh = std::min(p.nbk, (p.nbmax * p.qtile + kBlock - 1) / kBlock + 1);
-    const dim3 grid(copiers + fresh, p.hkv, p.batch);
+    const int64_t blocks = (int64_t)p.nbk * p.batch;
+    const int64_t tiles = (int64_t)((p.nbk + kCopyBlocks - 1) / kCopyBlocks) * p.batch;
+    const int fill = ((p.fp8 ? kPoolersFp8 : kPoolersBf16) * device_compute_units() + p.hkv - 1) / p.hkv;
+    const int poolers = (int)std::min<int64_t>(blocks, std::max(1, fill));
+    const int copiers = (int)std::min<int64_t>(tiles, (1 << 22) / p.hkv);   // within the largest grid
+    const unsigned grid = (unsigned)(poolers + copiers) * p.hkv;
     if (p.fp8)
-      pool_cached_kernel<1><<<grid, kThreads, 0, s>>>(p, out, cache, copiers);
+      pool_cached_kernel<1><<<grid, kThreads, 0, s>>>(p, out, cache, poolers, copiers);
     else
-      pool_cached_kernel<0><<<grid, kThreads, 0, s>>>(p, out, cache, copiers);
+      pool_cached_kernel<0><<<grid, kThreads, 0, s>>>(p, out, cache, poolers, copiers);
     return hipGetLastError();
   }
   const dim3 grid(p.nbk, p.hkv, p.batch);
