@@ -34,7 +34,11 @@
 // Latency-bound: all of it lies between the selection and the attention. Every
 // workgroup computes all costs (coalesced over the counts, kept in LDS) and
 // the class histogram, and writes the table entries of its own range of
-// units, so no workgroup waits for another.
+// units, so no workgroup waits for another. Past kCostCache units the costs are
+// computed again where they are needed: for all units in every round of the
+// budget and in the histogram, for its own range in the entries. The last is the
+// longest part, so that as many workgroups as otherwise share it (131072 units
+// 179 us, 234 with 4 of them; 36864 62 and 82).
 //
 // combine_kernel merges the parts of every split unit with the log-sum-exp
 // weights: M = max_u m_u, w_u = 2^(m_u - M), O = c_v sum_u w_u o_u /
@@ -391,9 +395,7 @@ int device_compute_units() {
 hipError_t launch_plan(const Problem& p, const KeptLists& kl, const Plan& plan, hipStream_t s) {
   if (p.batch == 0 || p.nbmax == 0) return hipSuccess;
   const int64_t units = (int64_t)p.batch * p.hkv * p.nbmax;
-  // past the cost cache every workgroup reads all counts three times: fewer of them
-  const int64_t most = units <= kCostCache ? kPlanGroups : 4;
-  const unsigned grid = (unsigned)std::max<int64_t>(1, std::min(most, units / kPlanUnits));
+  const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(kPlanGroups, units / kPlanUnits));
   const int wpu = plan.wpu;
   if (units <= kPlanFewUnits)
     plan_kernel<kPlanThreadsFew><<<grid, kPlanThreadsFew, 0, s>>>(p, kl, plan, wpu);
