@@ -72,10 +72,14 @@
  * usual log-sum-exp weights. The result equals the unsplit one up to
  * rounding (fp8: P~ is rounded against each part's own maximum).
  * kv_splits == 0 (the default) plans on the device after the selection:
- * only units costlier than a step budget are split, the budget being one
- * resident workgroup's share of the call's total cost (so a short chunk after
- * a long prefix, or a few dense heads, do not bound the run time), into at most
- * 64 parts. kv_splits == n >= 1 cuts every unit into n parts (1 = no splits).
+ * only units costlier than a step budget are split, into at most 64 parts, the
+ * budget being one resident workgroup's share of the call's total cost (so a
+ * short chunk after a long prefix, or a few dense heads, do not bound the run
+ * time), but at least 16 steps (8 for bf16 calls of few units), and more where
+ * the parts would not fit the workspace. A split fp8 output differs from the
+ * unsplit one by up to two roundings of its probabilities to e4m3 (0.03 in the
+ * relative 2-norm). kv_splits == n >= 1 cuts every unit into n parts (1 = no
+ * splits).
  *
  * Query tiles (Sec. 3.3 PackGQA and the per-tile index of Eq. csr)
  * --------------------------------------------------------------

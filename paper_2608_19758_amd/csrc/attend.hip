@@ -57,7 +57,6 @@
 // pruned J < Ja, with absolute positions; query rows and the LSE are indexed
 // by the local position.
 #include <algorithm>
-#include <utility>
 
 #include "kernels.h"
 
